@@ -125,7 +125,8 @@ struct Chain {
     GroupRec* rec = nullptr;      // [kRing]
     unsigned long long* stats = nullptr;  // [ST_N]
     unsigned long long* clk = nullptr;    // [2]
-    double* e_partial = nullptr;  // [(nb + 1) / 2]
+    double* e_partial = nullptr;  // [energy_pairs(nb) * e_split]
+    int e_split = 1;              // re-sum blocks per pair of super-rows
     EnergyAux* aux = nullptr;
     double* e_state = nullptr;
     double* sweep_tot = nullptr;  // [kMaxLaunchSweeps]
@@ -548,6 +549,7 @@ void fill_desc(mc_handle* h) {
         d.trace_cap = c.trace_cap;
         d.clk = c.clk;
         d.e_partial = c.e_partial;
+        d.e_split = c.e_split;
         d.aux = c.aux;
         d.e_state = c.e_state;
         d.sweep_tot = c.sweep_tot;
@@ -625,7 +627,7 @@ int launch_energy(mc_handle* h, int reset, int record_drift) {
         hipLaunchKernelGGL(energy_partial_kernel<float>, dim3(h->n_eitems), dim3(256), 0, h->stream,
                            h->d_desc, h->d_eitems, parity);
     HIPCHECK(h, hipGetLastError());
-    hipLaunchKernelGGL(energy_finalize_kernel, dim3((unsigned)h->chains.size()), dim3(64), 0, h->stream,
+    hipLaunchKernelGGL(energy_finalize_kernel, dim3((unsigned)h->chains.size()), dim3(256), 0, h->stream,
                        h->d_desc, reset, record_drift);
     HIPCHECK(h, hipGetLastError());
     return MC_OK;
@@ -669,7 +671,8 @@ int prepare_launch(mc_handle* h, int64_t n_sweeps, uint64_t seed) {
 
 // Running energies of the launch's sweeps, then the host's sweep count.
 int finish_launch(mc_handle* h, int64_t n_sweeps) {
-    hipLaunchKernelGGL(energy_scan_kernel, dim3((unsigned)h->chains.size()), dim3(256), 0, h->stream, h->d_desc,
+    const unsigned scan_threads = (unsigned)std::min<int64_t>(1024, 64 * n_sweeps);
+    hipLaunchKernelGGL(energy_scan_kernel, dim3((unsigned)h->chains.size()), dim3(scan_threads), 0, h->stream, h->d_desc,
                        (int32_t)n_sweeps, (int64_t)h->sweeps);
     HIPCHECK(h, hipGetLastError());
     h->sweeps += n_sweeps;
@@ -931,10 +934,12 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
     plan.add(&h->d_desc, sizeof(ChainDesc) * n_chains);
     plan.add(&h->d_wgmap, sizeof(int2) * (h->cap + n_chains));
     plan.add(&h->d_wgrange, sizeof(int2) * h->cap);
-    int n_e = 0, n_r = 0;
+    int n_e = 0, n_r = 0, e_pairs = 0;
     size_t max_hist = 0;
+    for (const Chain& c : h->chains) e_pairs += energy_pairs(c.nb);
     for (Chain& c : h->chains) {
-        n_e += (c.nb + 1) / 2;
+        c.e_split = energy_split(c.nb, e_pairs);
+        n_e += energy_pairs(c.nb) * c.e_split;
         n_r += c.nb;
         const size_t nt = c.species.size();
         max_hist = std::max(max_hist, nt * nt * (size_t)opt.rdf_bins);
@@ -954,7 +959,7 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
         plan.add(&c.rec, sizeof(GroupRec) * kRing);
         plan.add(&c.stats, sizeof(unsigned long long) * ST_N);
         plan.add(&c.clk, sizeof(unsigned long long) * 2);
-        plan.add(&c.e_partial, sizeof(double) * ((c.nb + 1) / 2));
+        plan.add(&c.e_partial, sizeof(double) * energy_pairs(c.nb) * c.e_split);
         plan.add(&c.aux, sizeof(EnergyAux));
         plan.add(&c.e_state, sizeof(double));
         plan.add(&c.sweep_tot, sizeof(double) * kMaxLaunchSweeps);
@@ -981,7 +986,7 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
     for (int k = 0; k < n_chains; ++k) {
         Chain& c = h->chains[k];
         const mc_chain_spec& sp = specs[k];
-        for (int p = 0; p < (c.nb + 1) / 2; ++p) eitems.push_back(BlockItem{k, p});
+        for (int p = 0; p < energy_pairs(c.nb) * c.e_split; ++p) eitems.push_back(BlockItem{k, p});
         for (int r = 0; r < c.nb; ++r) ritems.push_back(BlockItem{k, r});
         // positions carry the version tag of the sweep that produced them;
         // the initial state is the result of virtual sweeps -2 (parity 0)

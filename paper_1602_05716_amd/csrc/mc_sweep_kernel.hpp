@@ -96,7 +96,9 @@ struct ChainDesc {
     unsigned long long* clk;  // [2] wall clock at the launch start and when the
                               // chain's last group of the launch was published
     // energy bookkeeping and g(r) (auxiliary kernels)
-    double* e_partial;   // [(nb + 1) / 2] re-sum partials
+    double* e_partial;   // re-sum partials, one per block of the re-sum launch
+    int32_t e_split;     // re-sum blocks per pair of super-rows
+    int32_t pad1;
     void* aux;           // EnergyAux
     double* e_state;     // running energy
     double* sweep_tot;   // [max sweeps per launch] scratch of the scan
@@ -1492,24 +1494,37 @@ sweep_kernel(const ChainDesc* __restrict__ chains, const int2* __restrict__ wg_r
 }
 
 // Running energy after each sweep of a launch, one block per chain:
-// per-sweep totals of the group energy changes (each summed in group order),
-// then a serial prefix from the previous running energy.  Deterministic.
-__global__ void __launch_bounds__(256)
+// per-sweep totals of the group energy changes, one wave a sweep (lane l
+// sums the groups l, l + 64, ...; then a butterfly: the order depends on the
+// sweep alone, not on the launch it belongs to), then a serial prefix from
+// the previous running energy.  Deterministic.  Latency bound; with one
+// thread a sweep, summing its groups one after another, the scan of 100
+// sweeps of 512 groups took 155 us.
+__global__ void __launch_bounds__(1024)
 energy_scan_kernel(const ChainDesc* __restrict__ chains, int32_t n_sweeps, int64_t s0)
 {
     const ChainDesc& cd = chains[blockIdx.x];
     const int nb = cd.nb;
-    for (int s = threadIdx.x; s < n_sweeps; s += blockDim.x) {
+    const int lane = threadIdx.x & 63;
+    for (int s = threadIdx.x >> 6; s < n_sweeps; s += blockDim.x >> 6) {
         double t = 0.0;
-        for (int b = 0; b < nb; ++b) t += cd.de_group[(int64_t)s * nb + b];
-        cd.sweep_tot[s] = t;
+        for (int b = lane; b < nb; b += 64) t += cd.de_group[(int64_t)s * nb + b];
+        t = wave_sum(t);
+        if (lane == 0) cd.sweep_tot[s] = t;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         double e = *cd.e_state;
-        for (int s = 0; s < n_sweeps; ++s) {
-            e += cd.sweep_tot[s];
-            if (s0 + s < cd.e_capacity) cd.e_series[s0 + s] = e;
+        for (int k = 0; k < n_sweeps; k += 8) {
+            double v[8];  // loaded together: the prefix waits for memory once in eight sweeps
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = k + q < n_sweeps ? cd.sweep_tot[k + q] : 0.0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (k + q >= n_sweeps) break;
+                e += v[q];
+                if (s0 + k + q < cd.e_capacity) cd.e_series[s0 + k + q] = e;
+            }
         }
         *cd.e_state = e;
         // delayed-acceptance drift monitor: at the end of each window, the
