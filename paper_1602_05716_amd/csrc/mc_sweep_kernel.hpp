@@ -110,6 +110,15 @@ struct ChainDesc {
     double rdf_rc;       // centres need |x| <= rdf_rc
     unsigned long long* rdf_counts;   // [ntypes * ntypes * bins]
     unsigned long long* rdf_centres;  // [ntypes]
+    // ... the cell grid of its pair counts (cubic, over [-R, R]^3)
+    int32_t rdf_side;    // cells per side
+    int32_t pad2;
+    double rdf_org;      // R
+    double rdf_inv_h;    // 1 / side of a cell
+    int32_t* rdf_cells;  // [rdf_side^3] ions per cell, zero between samples
+    int32_t* rdf_start;  // [rdf_side^3 + 1] first ion of each cell in rdf_sorted
+    int32_t* rdf_rank;   // [npad] an ion's place in its cell
+    void* rdf_sorted;    // T4[npad]: {x, y, z, species} in cell order
     // delayed acceptance (kernels with DA = true only)
     const float* da_w;   // [kDaParams] network parameters (bfloat16 values held in float)
     const uint16_t* da_w1b;  // [128 x 128] W1 as bfloat16, transposed (row = hidden unit)
