@@ -476,7 +476,7 @@ int mc_mlp_grad(int32_t batch, const uint8_t* feats, const double* target, const
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid allocation): it calls no hipMalloc, hipFree or allocating library
  * routine.  Every buffer of the pass, and the staged inputs, live in one
- * file-scope device workspace of about 2.2 MB that each GPU the library
+ * file-scope device workspace of about 1.75 MB that each GPU the library
  * runs on holds until the process ends; batch is at most
  * MC_NOALLOC_MAX_BATCH (else MC_E_ARG).  The workspace is shared by every
  * call on a GPU and keeps the last call's contents (each pass overwrites

@@ -43,173 +43,369 @@ __device__ __forceinline__ uint16_t to_bf16(float v) {
 }
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
 
-// C[M x N] = op(A)[M x K] op(B)[K x N] (+ C if accumulate), bfloat16 inputs,
-// float sums on the matrix cores.  op(A)[m][k] = ta ? A[k * lda + m] :
-// A[m * lda + k]; op(B)[k][n] = tb ? B[n * ldb + k] : B[k * ldb + n].  A
-// workgroup of 4 waves computes a 64 x 64 block, each wave a 32 x 32 tile
-// with v_mfma_f32_32x32x8bf16_1k (lane l holds A[l % 32][4 (l / 32) + v],
+// One training step is three launches: rows_kernel (forward, residuals and
+// the backward pass down to dZ1, 32 pairs of rows a workgroup, everything
+// between the layers in LDS and registers), grads_kernel (the weight
+// gradients, the column sums and the loss over all rows) and adam_kernel.
+// Every sum keeps one fixed order, whatever the launch: a matrix product
+// accumulates its K index in ascending steps of 8 on the matrix cores, a
+// column sum runs over 256 strided partial sums and a tree.  Measured, a step
+// of 4096 moves: 24 + 22 + 5 us; as sixteen kernels with the activations in
+// memory between them and operands read as single bfloat16 values down the
+// columns, 2.6 ms.
+
+// Rows of bfloat16 values in LDS are padded to 132 (8-byte reads of 32 rows
+// then spread over the banks).
+constexpr int kRowPad = kHid + 4;
+typedef uint16_t row_t[kRowPad];
+
+// acc[t] += A[32 x 128] B[128 x 32] for two neighbouring column tiles: rows
+// row0.. of `a` ([row][k]) and rows col0.., col0 + 32.. of `b` ([column][k]),
+// v_mfma_f32_32x32x8bf16_1k (lane l holds A[l % 32][4 (l / 32) + v],
 // B[4 (l / 32) + v][l % 32], v = 0..3, and D[8 (r / 4) + 4 (l / 32) + r % 4]
-// [l % 32], r = 0..15).  M and N multiples of 64, K a multiple of 8.
+// [l % 32], r = 0..15).
+__device__ __forceinline__ void product_32x64(const row_t* a, int row0, const row_t* b, int col0, f32x16 (&acc)[2]) {
+    const int lane = threadIdx.x & 63, i = lane & 31, kq = (lane >> 5) * 4;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+#pragma unroll
+    for (int k0 = 0; k0 < kHid; k0 += 8) {
+        const bf16x4 av = *reinterpret_cast<const bf16x4*>(&a[row0 + i][k0 + kq]);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const bf16x4 bv = *reinterpret_cast<const bf16x4*>(&b[col0 + 32 * t + i][k0 + kq]);
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc[t], 0, 0, 0);
+        }
+    }
+}
+
+// What rows_kernel leaves for grads_kernel lies in blocks of 32 rows, [R / 32]
+// [128 columns][32]: row 8 s + 4 h + v of a block at 16 h + 4 s + v.  That is
+// the order in which a lane holds a column of a product (its 16 values go out
+// as one run) and in which it wants the operands of the next one over those
+// rows (4 steps of it in two 16-byte loads, a wave's loads without gaps).
+__device__ __forceinline__ size_t block32(int r, int col) {
+    return ((size_t)(r >> 5) * kHid + col) * 32 + (((r >> 2) & 1) * 16 + ((r >> 3) & 3) * 4 + (r & 3));
+}
+
+// What rows_kernel reads and leaves for grads_kernel.
+struct StepBuffers {
+    const float* Pw;                    // working parameters (bfloat16 values)
+    const uint16_t *W1t, *W2t, *W2b;    // bfloat16 W1 and W2, [column][k], and W2 as it is
+    uint16_t *X, *H1, *H2;              // blocks of rows, bfloat16: input and hidden layers
+    uint16_t *dZ2b, *dZ1b;              // blocks of rows, bfloat16
+    float *dZ2, *dZ1;                   // blocks of rows
+    float *out, *dout, *res;            // [R], [R], [B]
+    float* g;
+};
+
+struct RowsShared {
+    row_t x[64];      // input rows, then H2, then dZ2
+    row_t h[64];      // H1, then dZ1
+    row_t w1t[kHid], w2t[kHid], w2[kHid];
+    float b1[kHid], b2[kHid], w3[kHid];
+    float dout[64];
+};
+
+// Forward (and, with `back`, backward) of the pairs 32 blockIdx.x ..: rows
+// 0..31 of the tile are phi(x_i), rows 32..63 phi(x~_i) of the same moves
+// (global rows b and B + b).  feat: packed byte histograms [.][64] words, of
+// which pair b is entry idx[b] (idx NULL: b); y[b] = de[idx[b]] * inv_lB (y32
+// if given).  Bound: latency of one tile (13 us alone, 24 us for 128 tiles);
+// the four waves share it as 2 x 2 blocks of 32 rows by 64 columns.
 __global__ void __launch_bounds__(256)
-gemm_bf16_kernel(const uint16_t* __restrict__ A, int lda, int ta, const uint16_t* __restrict__ B, int ldb, int tb,
-                 float* __restrict__ C, int ldc, int K, int accumulate)
+rows_kernel(StepBuffers s, const uint32_t* __restrict__ feat, const int64_t* __restrict__ idx,
+            const double* __restrict__ de, double inv_lB, const float* __restrict__ y32, float b3, int B, int back)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m0 = blockIdx.x * 64 + (wave & 1) * 32, n0 = blockIdx.y * 64 + (wave >> 1) * 32;
-    const int i = lane & 31, kq = (lane >> 5) * 4;
+    __shared__ RowsShared sh;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int p0 = blockIdx.x * 32;
+    // all loads in flight before the first is used
+    constexpr int kPer = kHid * kIn / 8 / 256;
+    uint32_t fv[32 * 64 / 256];  // word tid % 64 (counts 4 w .. 4 w + 3) of pairs wave, wave + 4, ...
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int b = p0 + wave + 4 * j;
+        fv[j] = feat[(idx ? idx[b] : b) * 64 + lane];
+    }
+    auto weights = [&](row_t* dst, const uint16_t* src) {
+        uint4 v[kPer];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) v[j] = reinterpret_cast<const uint4*>(src)[tid + 256 * j];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            uint16_t* to = &dst[(tid + 256 * j) / (kIn / 8)][8 * (tid % (kIn / 8))];
+            *reinterpret_cast<uint2*>(to) = make_uint2(v[j].x, v[j].y);
+            *reinterpret_cast<uint2*>(to + 4) = make_uint2(v[j].z, v[j].w);
+        }
+    };
+    weights(sh.w1t, s.W1t);
+    weights(sh.w2t, s.W2t);
+    if (back) weights(sh.w2, s.W2b);
+    if (tid < kHid) {
+        sh.b1[tid] = s.Pw[oB1 + tid];
+        sh.b2[tid] = s.Pw[oB2 + tid];
+        sh.w3[tid] = s.Pw[oW3 + tid];
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        uint32_t pk[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) pk[q] = to_bf16((float)((fv[j] >> (8 * q)) & 0xFFu));
+        *reinterpret_cast<uint2*>(&sh.x[(lane >> 5) * 32 + wave + 4 * j][4 * (lane & 31)]) =
+            make_uint2(pk[0] | (pk[1] << 16), pk[2] | (pk[3] << 16));
+    }
+    __syncthreads();
+    const int row0 = 32 * (wave & 1), col0 = 64 * (wave >> 1);
+    auto row_of = [&](int r) { return row0 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4); };
+    auto grow_of = [&](int lr) { return (lr < 32 ? p0 : B + p0 - 32) + lr; };
+    // this lane's 16 rows of column col to the blocks of rows
+    const size_t run0 = block32(grow_of(row0 + 4 * (lane >> 5)), 0);
+    auto store_bf16 = [&](uint16_t* dst, int col, const uint32_t (&v)[8]) {
+        uint4* to = reinterpret_cast<uint4*>(dst + run0 + 32 * col);
+        to[0] = make_uint4(v[0], v[1], v[2], v[3]);
+        to[1] = make_uint4(v[4], v[5], v[6], v[7]);
+    };
+    auto store_f32 = [&](float* dst, int col, const float (&v)[16]) {
+        float4* to = reinterpret_cast<float4*>(dst + run0 + 32 * col);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) to[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    };
+    // relu(acc[t] + bias) to the LDS tile and, with `back`, to dst; its mask
+    auto relu_rows = [&](const f32x16& a, int col, float bias, row_t* tile, uint16_t* dst) {
+        uint32_t on = 0, pk[8];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float z = a[r] + bias;
+            on |= (uint32_t)(z > 0.f) << r;
+            const uint16_t hb = to_bf16(z > 0.f ? z : 0.f);
+            tile[row_of(r)][col] = hb;
+            pk[r / 2] = r & 1 ? pk[r / 2] | ((uint32_t)hb << 16) : hb;
+        }
+        if (back) store_bf16(dst, col, pk);
+        return on;
+    };
+    // gradient rows v to dst, as bfloat16 to dstb and, if given, the LDS tile
+    auto grad_rows = [&](const float (&v)[16], int col, float* dst, uint16_t* dstb, row_t* tile) {
+        uint32_t pk[8];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const uint16_t db = to_bf16(v[r]);
+            if (tile) tile[row_of(r)][col] = db;
+            pk[r / 2] = r & 1 ? pk[r / 2] | ((uint32_t)db << 16) : db;
+        }
+        store_f32(dst, col, v);
+        store_bf16(dstb, col, pk);
+    };
+    if (back) {
+        // the input: column tid / 2, the rows of half tid & 1, of both runs
+        const int col = tid >> 1, half = tid & 1;
+#pragma unroll
+        for (int run = 0; run < 2; ++run) {
+            uint32_t pk[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const row_t* from = sh.x + 32 * run + 8 * (q / 2) + 4 * half + 2 * (q & 1);
+                pk[q] = (uint32_t)from[0][col] | ((uint32_t)from[1][col] << 16);
+            }
+            uint4* to = reinterpret_cast<uint4*>(s.X + block32(grow_of(32 * run + 4 * half), col));
+            to[0] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+            to[1] = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+        }
+    }
+    f32x16 acc[2];
+    uint32_t on1[2], on2[2];  // Z > 0, bit r
+    product_32x64(sh.x, row0, sh.w1t, col0, acc);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int col = col0 + 32 * t + (lane & 31);
+        on1[t] = relu_rows(acc[t], col, sh.b1[col], sh.h, s.H1);
+    }
+    __syncthreads();  // (the input rows are no longer needed from here on)
+    product_32x64(sh.h, row0, sh.w2t, col0, acc);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int col = col0 + 32 * t + (lane & 31);
+        on2[t] = relu_rows(acc[t], col, sh.b2[col], sh.x, s.H2);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        // out[r] = b3 + sum_k H2[r][k] w3[k], k ascending; a lane a row
+        float o = b3;
+#pragma unroll 32
+        for (int k = 0; k < kHid; ++k) o = __builtin_fmaf(from_bf16(sh.x[lane][k]), sh.w3[k], o);
+        s.out[grow_of(lane)] = o;
+        if (back) {
+            const float o_new = __shfl(o, 32 + (lane & 31), 64), o_old = __shfl(o, lane & 31, 64);
+            const int b = p0 + (lane & 31);
+            const float y = y32 ? y32[b] : (float)(de[idx ? idx[b] : b] * inv_lB);
+            const float r = o_new - o_old - y;
+            const float g = 2.f * r / (float)B;
+            const float d = lane < 32 ? -g : g;
+            if (lane < 32) s.res[b] = r;
+            s.dout[grow_of(lane)] = d;
+            sh.dout[lane] = d;
+        }
+    }
+    if (!back) return;
+    __syncthreads();
+    // dZ2[r][h] = dout[r] w3[h] [Z2 > 0]
+    float d[16];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int col = col0 + 32 * t + (lane & 31);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) d[r] = ((on2[t] >> r) & 1u) ? sh.dout[row_of(r)] * sh.w3[col] : 0.f;
+        grad_rows(d, col, s.dZ2, s.dZ2b, sh.x);
+    }
+    __syncthreads();
+    product_32x64(sh.x, row0, sh.w2, col0, acc);  // dH1 = dZ2 W2^T
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int col = col0 + 32 * t + (lane & 31);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) d[r] = ((on1[t] >> r) & 1u) ? acc[t][r] : 0.f;
+        grad_rows(d, col, s.dZ1, s.dZ1b, nullptr);
+    }
+}
+
+// A 32 x 32 tile of C[128 x 128] = A^T B over K = R rows, A and B in blocks
+// of 32 rows: one wave, accumulating steps of 8 rows in ascending order (the
+// order fixes the sum, so K is not split).  Bound: the chain of dependent
+// matrix instructions, 1024 of them in 22 us at R = 8192; the operands travel
+// kAhead blocks (4 steps each) ahead, and a tile has a compute unit to itself:
+// four tiles on one, 56 us.
+constexpr int kAhead = 8;
+__device__ __forceinline__ void grad_tile(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, int R, int m0,
+                                          int n0, float* __restrict__ C) {
+    const int lane = threadIdx.x & 63, i = lane & 31, half = lane >> 5;
+    const uint4* a = reinterpret_cast<const uint4*>(A) + (m0 + i) * 4 + 2 * half;
+    const uint4* b = reinterpret_cast<const uint4*>(B) + (n0 + i) * 4 + 2 * half;
     f32x16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    for (int k0 = 0; k0 < K; k0 += 8) {
-        bf16x4 a, b;
+    const int blocks = R / 32;
+    uint4 av[kAhead][2], bv[kAhead][2];
+    auto load = [&](int q, int k) {  // block k, or the last one again
+        const size_t at = (size_t)(k < blocks ? k : blocks - 1) * (kHid * 4);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int k = k0 + kq + v;
-            a[v] = (short)(ta ? A[(size_t)k * lda + (m0 + i)] : A[(size_t)(m0 + i) * lda + k]);
-            b[v] = (short)(tb ? B[(size_t)(n0 + i) * ldb + k] : B[(size_t)k * ldb + (n0 + i)]);
+        for (int u = 0; u < 2; ++u) {
+            av[q][u] = a[at + u];
+            bv[q][u] = b[at + u];
         }
-        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, acc, 0, 0, 0);
+    };
+    auto steps = [&](int q) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            struct two {
+                bf16x4 v[2];
+            };
+            const two x = __builtin_bit_cast(two, av[q][u]), y = __builtin_bit_cast(two, bv[q][u]);
+            acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(x.v[0], y.v[0], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(x.v[1], y.v[1], acc, 0, 0, 0);
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) load(q, q);
+    int k = 0;
+    for (; k + kAhead <= blocks; k += kAhead) {
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            steps(q);
+            load(q, k + q + kAhead);
+        }
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int row = m0 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-        float* dst = C + (size_t)row * ldc + (n0 + i);
-        *dst = accumulate ? *dst + acc[r] : acc[r];
+    for (int q = 0; q < kAhead; ++q)
+        if (k + q < blocks) steps(q);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) C[(m0 + 8 * (r / 4) + 4 * half + (r % 4)) * kHid + n0 + i] = acc[r];
+}
+
+// Sum over the 256 threads' values, a tree in thread order.
+template <typename T>
+__device__ __forceinline__ T block_tree(T v, T* part) {
+    part[threadIdx.x] = v;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
+        __syncthreads();
     }
+    return part[0];
 }
 
-// Batch rows from logged moves: row b = phi(x_i) of pair b, row B + b =
-// phi(x~_i); counts as bfloat16 (exact); y[b] = dE / l_B.
-__global__ void gather_kernel(const uint32_t* __restrict__ feat, const double* __restrict__ de,
-                              const int64_t* __restrict__ idx, int B, double inv_lB, uint16_t* __restrict__ X,
-                              float* __restrict__ y)
+// The gradient over all rows, one launch: blocks 0..31 the 32 tiles of dW2
+// = H1^T dZ2 and dW1 = X^T dZ1 (one wave each), then a block per column of the w3, b2 and b1
+// gradients, one for b3 and one for the loss mean(res^2) -- the column sums
+// run beside the serial matrix chains.
+constexpr int kGradTileBlocks = 32, kGradBlocks = kGradTileBlocks + 3 * kHid + 2;
+__global__ void __launch_bounds__(256)
+grads_kernel(StepBuffers s, int B, double* __restrict__ loss)
 {
-    const int b = blockIdx.x;
-    const int64_t m = idx[b];
-    for (int k = threadIdx.x; k < 2 * kIn; k += blockDim.x) {
-        const uint32_t w = feat[m * 64 + (k >> 2)];
-        const float c = (float)((w >> (8 * (k & 3))) & 0xFFu);
-        const int row = k < kIn ? b : B + b;
-        X[(size_t)row * kIn + (k & (kIn - 1))] = to_bf16(c);
+    __shared__ double part64[256];
+    __shared__ float part[256];
+    const int R = 2 * B, tid = threadIdx.x;
+    int q = blockIdx.x;
+    if (q < kGradTileBlocks) {
+        if (tid >= 64) return;
+        const int m0 = 32 * ((q >> 2) & 3), n0 = 32 * (q & 3);
+        if (q < 16)
+            grad_tile(s.H1, s.dZ2b, R, m0, n0, s.g + oW2);
+        else
+            grad_tile(s.X, s.dZ1b, R, m0, n0, s.g + oW1);
+        return;
     }
-    if (threadIdx.x == 0) y[b] = (float)(de[m] * inv_lB);
-}
-
-// Same from host-given byte histograms [B][256] (gradient checks).
-__global__ void gather_bytes_kernel(const uint8_t* __restrict__ f, int B, uint16_t* __restrict__ X)
-{
-    const int b = blockIdx.x;
-    for (int k = threadIdx.x; k < 2 * kIn; k += blockDim.x) {
-        const int row = k < kIn ? b : B + b;
-        X[(size_t)row * kIn + (k & (kIn - 1))] = to_bf16((float)f[(size_t)b * 2 * kIn + k]);
+    q -= kGradTileBlocks;
+    if (q < 3 * kHid + 1) {
+        const int k = q & (kHid - 1), what = q / kHid;
+        float acc = 0.f;
+        if (what == 0) {
+#pragma unroll 8
+            for (int r = tid; r < R; r += 256) acc += s.dout[r] * from_bf16(s.H2[block32(r, k)]);
+        } else if (what == 3) {
+#pragma unroll 8
+            for (int r = tid; r < R; r += 256) acc += s.dout[r];
+        } else {
+            const float* m = what == 1 ? s.dZ2 : s.dZ1;
+#pragma unroll 8
+            for (int r = tid; r < R; r += 256) acc += m[block32(r, k)];
+        }
+        const float t = block_tree(acc, part);
+        if (tid == 0) s.g[(what == 0 ? oW3 : what == 1 ? oB2 : what == 2 ? oB1 : oB3) + k] = t;
+        return;
     }
-}
-
-// Z += bias (in place, float); H = bf16(relu(Z)).
-__global__ void bias_relu_kernel(float* __restrict__ Z, const float* __restrict__ bias, uint16_t* __restrict__ H,
-                                 int rows)
-{
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)rows * kHid) return;
-    const float z = Z[t] + bias[t % kHid];
-    Z[t] = z;
-    H[t] = to_bf16(z > 0.f ? z : 0.f);
-}
-
-// out[r] = b3 + sum_k H2[r][k] w3[k], k ascending.
-__global__ void out_kernel(const uint16_t* __restrict__ H2, const float* __restrict__ w3, float b3,
-                           float* __restrict__ out, int rows)
-{
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= rows) return;
-    float o = b3;
-    for (int k = 0; k < kHid; ++k) o = __builtin_fmaf(from_bf16(H2[(size_t)r * kHid + k]), w3[k], o);
-    out[r] = o;
-}
-
-// Residuals, loss and the gradient with respect to the outputs.
-__global__ void loss_kernel(const float* __restrict__ out, const float* __restrict__ y, int B,
-                            float* __restrict__ dout, double* __restrict__ loss)
-{
-    __shared__ double part[256];
     double acc = 0.0;
-    for (int b = threadIdx.x; b < B; b += blockDim.x) {
-        const float r = out[B + b] - out[b] - y[b];
+    for (int b = tid; b < B; b += 256) {
+        const float r = s.res[b];
         acc += (double)r * (double)r;
-        const float g = 2.f * r / (float)B;
-        dout[B + b] = g;
-        dout[b] = -g;
     }
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-        __syncthreads();
+    const double t = block_tree(acc, part64);
+    if (tid == 0) *loss = t / (double)B;
+}
+
+// Parameter t's working copies: the bfloat16 value in float, and in the
+// matrices of the hidden layers ([column][k], and W2 also as it is).
+__device__ __forceinline__ void store_working(float p, int t, float* Pw, uint16_t* W1t, uint16_t* W2t, uint16_t* W2b) {
+    const uint16_t hb = to_bf16(p);
+    Pw[t] = from_bf16(hb);
+    if (t >= oW1 && t < oB1) {
+        const int e = t - oW1;
+        W1t[(e % kHid) * kIn + e / kHid] = hb;
     }
-    if (threadIdx.x == 0) *loss = part[0] / (double)B;
-}
-
-// dZ2[r][h] = dout[r] w3[h] [Z2 > 0] (float and bfloat16 copies).
-__global__ void back_out_kernel(const float* __restrict__ dout, const float* __restrict__ w3,
-                                const float* __restrict__ Z2, float* __restrict__ dZ2, uint16_t* __restrict__ dZ2b,
-                                int rows)
-{
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)rows * kHid) return;
-    const float g = Z2[t] > 0.f ? dout[t / kHid] * w3[t % kHid] : 0.f;
-    dZ2[t] = g;
-    dZ2b[t] = to_bf16(g);
-}
-
-// dZ1 = dH1 [Z1 > 0] (in place in dH1) and its bfloat16 copy.
-__global__ void back_relu_kernel(float* __restrict__ dH, const float* __restrict__ Z, uint16_t* __restrict__ dHb,
-                                 int rows)
-{
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)rows * kHid) return;
-    const float g = Z[t] > 0.f ? dH[t] : 0.f;
-    dH[t] = g;
-    dHb[t] = to_bf16(g);
-}
-
-// Column sums of a [rows x 128] float matrix (bias gradients), and
-// sum_r dout[r] H2[r][k] (w3 gradient) when H2 is given; one block per column.
-__global__ void colsum_kernel(const float* __restrict__ M, const float* __restrict__ dout,
-                              const uint16_t* __restrict__ H2, int rows, float* __restrict__ g)
-{
-    __shared__ float part[256];
-    const int k = blockIdx.x;
-    float acc = 0.f;
-    for (int r = threadIdx.x; r < rows; r += blockDim.x)
-        acc += H2 ? dout[r] * from_bf16(H2[(size_t)r * kHid + k]) : M[(size_t)r * kHid + k];
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-        __syncthreads();
+    if (t >= oW2 && t < oB2) {
+        const int e = t - oW2;
+        W2t[(e % kHid) * kHid + e / kHid] = hb;
+        W2b[e] = hb;
     }
-    if (threadIdx.x == 0) g[k] = part[0];
 }
 
-__global__ void sum_kernel(const float* __restrict__ v, int n, float* __restrict__ out)
-{
-    __shared__ float part[256];
-    float acc = 0.f;
-    for (int r = threadIdx.x; r < n; r += blockDim.x) acc += v[r];
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = part[0];
-}
-
-// Adam on the float master weights; refreshes the bfloat16-valued working
-// copy (float) and the bfloat16 matrices of both hidden layers.
+// Adam on the float master weights; refreshes the working copies.
 __global__ void adam_kernel(float* __restrict__ P, float* __restrict__ m, float* __restrict__ v,
                             const float* __restrict__ g, int n, float lr, float b1, float b2, float eps, float c1,
-                            float c2, float* __restrict__ Pw, uint16_t* __restrict__ W1b, uint16_t* __restrict__ W2b)
+                            float c2, float* __restrict__ Pw, uint16_t* __restrict__ W1t, uint16_t* __restrict__ W2t,
+                            uint16_t* __restrict__ W2b)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n) return;
@@ -220,122 +416,97 @@ __global__ void adam_kernel(float* __restrict__ P, float* __restrict__ m, float*
     v[t] = vt;
     const float p = P[t] - lr * (mt / c1) / (sqrtf(vt / c2) + eps);
     P[t] = p;
-    const uint16_t hb = to_bf16(p);
-    Pw[t] = from_bf16(hb);
-    if (t >= oW1 && t < oB1) W1b[t - oW1] = hb;
-    if (t >= oW2 && t < oB2) W2b[t - oW2] = hb;
+    store_working(p, t, Pw, W1t, W2t, W2b);
 }
 
 // Working copies from float master weights (bfloat16 values).
-__global__ void refresh_kernel(const float* __restrict__ P, int n, float* __restrict__ Pw, uint16_t* __restrict__ W1b,
-                               uint16_t* __restrict__ W2b)
+__global__ void refresh_kernel(const float* __restrict__ P, int n, float* __restrict__ Pw, uint16_t* __restrict__ W1t,
+                               uint16_t* __restrict__ W2t, uint16_t* __restrict__ W2b)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const uint16_t hb = to_bf16(P[t]);
-    Pw[t] = from_bf16(hb);
-    if (t >= oW1 && t < oB1) W1b[t - oW1] = hb;
-    if (t >= oW2 && t < oB2) W2b[t - oW2] = hb;
+    if (t < n) store_working(P[t], t, Pw, W1t, W2t, W2b);
 }
 
-// Device workspace of the network for batches of up to Bmax pairs.
+// Device workspace of the network for batches of up to B pairs.
 struct Net {
-    int Bmax = 0;
     float *P = nullptr, *Pw = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
-    uint16_t *W1b = nullptr, *W2b = nullptr;
+    uint16_t *W1t = nullptr, *W2t = nullptr, *W2b = nullptr;
     uint16_t *X = nullptr, *H1 = nullptr, *H2 = nullptr, *dZ2b = nullptr, *dZ1b = nullptr;
-    float *Z1 = nullptr, *Z2 = nullptr, *out = nullptr, *dout = nullptr, *dZ2 = nullptr, *dH1 = nullptr, *y = nullptr;
-    int64_t* idx = nullptr;
+    float *out = nullptr, *dout = nullptr, *res = nullptr, *dZ2 = nullptr, *dZ1 = nullptr, *y = nullptr;
     double* loss = nullptr;
-    std::vector<void*> all;
+    uint8_t* feat = nullptr;  // staged byte histograms (gradient pass only)
+    void* own = nullptr;      // the one allocation behind the pointers, if this object made it
     hipStream_t s = nullptr;
 
-    template <typename Q>
-    bool get(Q** p, size_t bytes) {
-        void* q = nullptr;
-        if (hipMalloc(&q, bytes ? bytes : 16) != hipSuccess) return false;
-        all.push_back(q);
-        *p = (Q*)q;
-        return true;
-    }
     // every buffer of a batch of B moves (the optimizer's moments only when
-    // training), each obtained from take(&pointer, bytes)
+    // training, the staged histograms only when not), each obtained from
+    // take(&pointer, bytes)
     template <typename Take>
     static bool layout(Net& n, int B, bool train, Take&& take) {
         const size_t R = 2 * (size_t)B;
         return take(&n.P, 4 * kNP) && take(&n.Pw, 4 * kNP) && (!train || (take(&n.m, 4 * kNP) && take(&n.v, 4 * kNP))) &&
-               take(&n.g, 4 * kNP) && take(&n.W1b, 2 * kIn * kHid) && take(&n.W2b, 2 * kHid * kHid) &&
-               take(&n.X, 2 * R * kIn) && take(&n.H1, 2 * R * kHid) && take(&n.H2, 2 * R * kHid) &&
-               take(&n.dZ2b, 2 * R * kHid) && take(&n.dZ1b, 2 * R * kHid) && take(&n.Z1, 4 * R * kHid) &&
-               take(&n.Z2, 4 * R * kHid) && take(&n.out, 4 * R) && take(&n.dout, 4 * R) &&
-               take(&n.dZ2, 4 * R * kHid) && take(&n.dH1, 4 * R * kHid) && take(&n.y, 4 * (size_t)B) &&
-               take(&n.idx, 8 * (size_t)B) && take(&n.loss, 8);
+               take(&n.g, 4 * kNP) && take(&n.W1t, 2 * kIn * kHid) && take(&n.W2t, 2 * kHid * kHid) &&
+               take(&n.W2b, 2 * kHid * kHid) && take(&n.X, 2 * R * kIn) && take(&n.H1, 2 * R * kHid) &&
+               take(&n.H2, 2 * R * kHid) && take(&n.dZ2b, 2 * R * kHid) && take(&n.dZ1b, 2 * R * kHid) &&
+               take(&n.out, 4 * R) && take(&n.dout, 4 * R) && take(&n.res, 4 * (size_t)B) &&
+               take(&n.dZ2, 4 * R * kHid) && take(&n.dZ1, 4 * R * kHid) && take(&n.y, 4 * (size_t)B) &&
+               take(&n.loss, 8) && (train || take(&n.feat, (size_t)B * 2 * kIn));
     }
-    bool init(int B, hipStream_t stream) {
-        Bmax = B;
-        s = stream;
-        return layout(*this, B, true, [this](auto** p, size_t bytes) { return get(p, bytes); });
-    }
-    // the buffers of a gradient pass (no optimizer moments) carved out of
-    // caller-provided device memory [base, base + cap); nothing is allocated
-    // and nothing is freed by the destructor
-    bool carve(int B, unsigned char* base, size_t cap, size_t* used) {
-        Bmax = B;
+    // bytes of the layout, each buffer rounded up to 256
+    static size_t bytes(int B, bool train) {
+        Net n;
         size_t at = 0;
-        auto take = [&](auto** p, size_t bytes) {
-            const size_t a = (bytes + 255) & ~(size_t)255;
+        layout(n, B, train, [&](auto**, size_t b) {
+            at += (b + 255) & ~(size_t)255;
+            return true;
+        });
+        return at;
+    }
+    // the buffers carved out of device memory [base, base + cap)
+    bool carve(int B, bool train, unsigned char* base, size_t cap) {
+        size_t at = 0;
+        return layout(*this, B, train, [&](auto** p, size_t b) {
+            const size_t a = (b + 255) & ~(size_t)255;
             if (at + a > cap) return false;
             *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(base + at);
             at += a;
             return true;
-        };
-        const bool ok = layout(*this, B, false, take);
-        *used = at;
-        return ok;
+        });
+    }
+    // ... of an allocation of this object's own
+    bool init(int B, bool train, hipStream_t stream) {
+        s = stream;
+        const size_t cap = bytes(B, train);
+        return hipMalloc(&own, cap) == hipSuccess && carve(B, train, (unsigned char*)own, cap);
     }
     ~Net() {
+        if (!own) return;
         if (s) (void)hipStreamSynchronize(s);
-        for (void* q : all) (void)hipFree(q);
+        (void)hipFree(own);
     }
     bool upload_params(const std::vector<float>& p) {
         if (hipMemcpy(P, p.data(), 4 * kNP, hipMemcpyHostToDevice) != hipSuccess) return false;
         if (m && hipMemset(m, 0, 4 * kNP) != hipSuccess) return false;
         if (v && hipMemset(v, 0, 4 * kNP) != hipSuccess) return false;
-        hipLaunchKernelGGL(refresh_kernel, dim3((kNP + 255) / 256), dim3(256), 0, s, P, kNP, Pw, W1b, W2b);
+        hipLaunchKernelGGL(refresh_kernel, dim3((kNP + 255) / 256), dim3(256), 0, s, P, kNP, Pw, W1t, W2t, W2b);
         return hipGetLastError() == hipSuccess;
     }
-    void gemm(const uint16_t* A, int lda, int ta, const uint16_t* B, int ldb, int tb, float* C, int ldc, int M, int N,
-              int K, int accumulate) {
-        hipLaunchKernelGGL(gemm_bf16_kernel, dim3(M / 64, N / 64), dim3(256), 0, s, A, lda, ta, B, ldb, tb, C, ldc, K,
-                           accumulate);
+    StepBuffers buffers() const {
+        return StepBuffers{Pw, W1t, W2t, W2b, X, H1, H2, dZ2b, dZ1b, dZ2, dZ1, out, dout, res, g};
     }
-    // forward over the R = 2B rows of X
-    void forward(int B) {
-        const int R = 2 * B;
-        const int ew = (R * kHid + 255) / 256;
-        gemm(X, kIn, 0, W1b, kHid, 0, Z1, kHid, R, kHid, kIn, 0);
-        hipLaunchKernelGGL(bias_relu_kernel, dim3(ew), dim3(256), 0, s, Z1, Pw + oB1, H1, R);
-        gemm(H1, kHid, 0, W2b, kHid, 0, Z2, kHid, R, kHid, kHid, 0);
-        hipLaunchKernelGGL(bias_relu_kernel, dim3(ew), dim3(256), 0, s, Z2, Pw + oB2, H2, R);
+    // outputs of B moves (pairs idx of the histograms, or all in order)
+    void outputs(int B, const uint32_t* f, const int64_t* idx, float b3, float* to) {
+        StepBuffers b = buffers();
+        b.out = to;
+        hipLaunchKernelGGL(rows_kernel, dim3(B / 32), dim3(256), 0, s, b, f, idx, (const double*)nullptr, 0.0,
+                           (const float*)nullptr, b3, B, 0);
     }
-    void outputs(int B, float b3) {
-        const int R = 2 * B;
-        hipLaunchKernelGGL(out_kernel, dim3((R + 255) / 256), dim3(256), 0, s, H2, Pw + oW3, b3, out, R);
-    }
-    // loss and gradient (into g) of the batch in X / y
-    void backward(int B) {
-        const int R = 2 * B;
-        const int ew = (R * kHid + 255) / 256;
-        hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(256), 0, s, out, y, B, dout, loss);
-        hipLaunchKernelGGL(colsum_kernel, dim3(kHid), dim3(256), 0, s, nullptr, dout, H2, R, g + oW3);
-        hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(256), 0, s, dout, R, g + oB3);
-        hipLaunchKernelGGL(back_out_kernel, dim3(ew), dim3(256), 0, s, dout, Pw + oW3, Z2, dZ2, dZ2b, R);
-        hipLaunchKernelGGL(colsum_kernel, dim3(kHid), dim3(256), 0, s, dZ2, nullptr, nullptr, R, g + oB2);
-        gemm(H1, kHid, 1, dZ2b, kHid, 0, g + oW2, kHid, kHid, kHid, R, 0);   // dW2 = H1^T dZ2
-        gemm(dZ2b, kHid, 0, W2b, kHid, 1, dH1, kHid, R, kHid, kHid, 0);      // dH1 = dZ2 W2^T
-        hipLaunchKernelGGL(back_relu_kernel, dim3(ew), dim3(256), 0, s, dH1, Z1, dZ1b, R);
-        hipLaunchKernelGGL(colsum_kernel, dim3(kHid), dim3(256), 0, s, dH1, nullptr, nullptr, R, g + oB1);
-        gemm(X, kIn, 1, dZ1b, kHid, 0, g + oW1, kHid, kIn, kHid, R, 0);      // dW1 = X^T dZ1
+    // loss (into *l) and gradient (into g) of B moves; targets de[idx] inv_lB,
+    // or y where de is NULL
+    void gradient(int B, const uint32_t* f, const int64_t* idx, const double* de, double inv_lB, float b3, double* l) {
+        hipLaunchKernelGGL(rows_kernel, dim3(B / 32), dim3(256), 0, s, buffers(), f, idx, de, inv_lB,
+                           (const float*)(de ? nullptr : y), b3, B, 1);
+        hipLaunchKernelGGL(grads_kernel, dim3(kGradBlocks), dim3(256), 0, s, buffers(), B, l);
     }
 };
 
@@ -358,18 +529,18 @@ int noalloc_fail(int code, const std::string& msg) {
     return code;
 }
 
-// Bytes of the buffers Net::carve takes for a gradient pass of B moves plus
-// the staged byte histograms (each piece rounded up to 256 bytes).
+// Bytes of the buffers Net::carve takes for a gradient pass of B moves (each
+// piece rounded up to 256 bytes).
 constexpr size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 constexpr size_t grad_pass_bytes(int B) {
     const size_t R = 2 * (size_t)B;
-    return 3 * round256(4 * (size_t)kNP) + round256(2 * kIn * kHid) + round256(2 * kHid * kHid) +
-           round256(2 * R * kIn) + 4 * round256(2 * R * kHid) + 4 * round256(4 * R * kHid) + 2 * round256(4 * R) +
-           round256(4 * (size_t)B) + round256(8 * (size_t)B) + round256(8) + round256((size_t)B * 2 * kIn);
+    return 3 * round256(4 * (size_t)kNP) + 3 * round256(2 * kIn * kHid) + 5 * round256(2 * R * kHid) +
+           2 * round256(4 * R) + 2 * round256(4 * R * kHid) + 2 * round256(4 * (size_t)B) + round256(8) +
+           round256((size_t)B * 2 * kIn);
 }
 
 // Largest batch of mc_mlp_grad_noalloc and its device workspace: one
-// file-scope array, about 2.2 MB, that every GPU the library runs on holds
+// file-scope array, about 1.75 MB, that every GPU the library runs on holds
 // until the process ends.  Host code never names it directly: its device
 // address comes from hipGetSymbolAddress, once per device.
 constexpr int kNoAllocBatch = MC_NOALLOC_MAX_BATCH;
@@ -401,6 +572,41 @@ unsigned char* device_scratch() {
     return g_scratch_ptr[dev];
 }
 
+// One gradient pass on host data in the buffers of `net` (params as given,
+// p the same in float), on the null stream.
+int gradient_pass(Net& net, int batch, const uint8_t* feats, const double* target, const double* params,
+                  const std::vector<float>& p, double* loss, double* grad, std::string& err) {
+    if (!net.upload_params(p)) {
+        err = "parameter upload failed";
+        return MC_E_DEVICE;
+    }
+    std::vector<float> y(batch);
+    for (int b = 0; b < batch; ++b) y[b] = (float)target[b];
+    if (hipMemcpy(net.feat, feats, (size_t)batch * 2 * kIn, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(net.y, y.data(), 4 * (size_t)batch, hipMemcpyHostToDevice) != hipSuccess) {
+        err = "input upload failed";
+        return MC_E_DEVICE;
+    }
+    // (byte k of a histogram is byte k & 3 of its word k / 4)
+    net.gradient(batch, reinterpret_cast<const uint32_t*>(net.feat), nullptr, nullptr, 0.0, round_bf16_host(params[oB3]),
+                 net.loss);
+    if (hipDeviceSynchronize() != hipSuccess || hipGetLastError() != hipSuccess) {
+        err = "the gradient pass failed on the device";
+        return MC_E_DEVICE;
+    }
+    std::vector<float> g(kNP);
+    double l = 0.0;
+    if (hipMemcpy(g.data(), net.g, 4 * kNP, hipMemcpyDeviceToHost) != hipSuccess ||
+        hipMemcpy(&l, net.loss, 8, hipMemcpyDeviceToHost) != hipSuccess) {
+        err = "output download failed";
+        return MC_E_DEVICE;
+    }
+    if (loss) *loss = l;
+    if (grad)
+        for (int k = 0; k < kNP; ++k) grad[k] = g[k];
+    return MC_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -415,29 +621,9 @@ int mc_mlp_grad(int32_t batch, const uint8_t* feats, const double* target, const
         p[k] = (float)params[k];
     }
     Net net;
-    if (!net.init(batch, nullptr)) return MC_E_OOM;
-    if (!net.upload_params(p)) return MC_E_DEVICE;
-    uint8_t* dfeat = nullptr;
-    if (!net.get(&dfeat, (size_t)batch * 2 * kIn)) return MC_E_OOM;
-    std::vector<float> y(batch);
-    for (int b = 0; b < batch; ++b) y[b] = (float)target[b];
-    if (hipMemcpy(dfeat, feats, (size_t)batch * 2 * kIn, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(net.y, y.data(), 4 * (size_t)batch, hipMemcpyHostToDevice) != hipSuccess)
-        return MC_E_DEVICE;
-    hipLaunchKernelGGL(gather_bytes_kernel, dim3(batch), dim3(256), 0, nullptr, dfeat, batch, net.X);
-    net.forward(batch);
-    net.outputs(batch, round_bf16_host(params[oB3]));
-    net.backward(batch);
-    if (hipDeviceSynchronize() != hipSuccess || hipGetLastError() != hipSuccess) return MC_E_DEVICE;
-    std::vector<float> g(kNP);
-    double l = 0.0;
-    if (hipMemcpy(g.data(), net.g, 4 * kNP, hipMemcpyDeviceToHost) != hipSuccess ||
-        hipMemcpy(&l, net.loss, 8, hipMemcpyDeviceToHost) != hipSuccess)
-        return MC_E_DEVICE;
-    if (loss) *loss = l;
-    if (grad)
-        for (int k = 0; k < kNP; ++k) grad[k] = g[k];
-    return MC_OK;
+    if (!net.init(batch, false, nullptr)) return MC_E_OOM;
+    std::string err;
+    return gradient_pass(net, batch, feats, target, params, p, loss, grad, err);
 }
 
 int mc_mlp_grad_noalloc(int32_t batch, const uint8_t* feats, const double* target, const double* params,
@@ -455,33 +641,11 @@ int mc_mlp_grad_noalloc(int32_t batch, const uint8_t* feats, const double* targe
     unsigned char* ws = device_scratch();
     if (!ws) return noalloc_fail(MC_E_DEVICE, g_train_error);
     Net net;
-    size_t used = 0;
-    uint8_t* dfeat = nullptr;
-    if (!net.carve(batch, ws, kScratchBytes, &used) ||
-        used + round256((size_t)batch * 2 * kIn) > kScratchBytes)
+    if (!net.carve(batch, false, ws, kScratchBytes))
         return noalloc_fail(MC_E_STATE, "the buffers of the pass do not fit the workspace");
-    dfeat = ws + used;
-    if (!net.upload_params(p)) return noalloc_fail(MC_E_DEVICE, "parameter upload failed");
-    std::vector<float> y(batch);
-    for (int b = 0; b < batch; ++b) y[b] = (float)target[b];
-    if (hipMemcpy(dfeat, feats, (size_t)batch * 2 * kIn, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(net.y, y.data(), 4 * (size_t)batch, hipMemcpyHostToDevice) != hipSuccess)
-        return noalloc_fail(MC_E_DEVICE, "input upload failed");
-    hipLaunchKernelGGL(gather_bytes_kernel, dim3(batch), dim3(256), 0, nullptr, dfeat, batch, net.X);
-    net.forward(batch);
-    net.outputs(batch, round_bf16_host(params[oB3]));
-    net.backward(batch);
-    if (hipDeviceSynchronize() != hipSuccess || hipGetLastError() != hipSuccess)
-        return noalloc_fail(MC_E_DEVICE, "the gradient pass failed on the device");
-    std::vector<float> g(kNP);
-    double l = 0.0;
-    if (hipMemcpy(g.data(), net.g, 4 * kNP, hipMemcpyDeviceToHost) != hipSuccess ||
-        hipMemcpy(&l, net.loss, 8, hipMemcpyDeviceToHost) != hipSuccess)
-        return noalloc_fail(MC_E_DEVICE, "output download failed");
-    if (loss) *loss = l;
-    if (grad)
-        for (int k = 0; k < kNP; ++k) grad[k] = g[k];
-    return MC_OK;
+    std::string err;
+    const int rc = gradient_pass(net, batch, feats, target, params, p, loss, grad, err);
+    return rc == MC_OK ? MC_OK : noalloc_fail(rc, err);
 }
 
 int mc_train_surrogate(mc_handle* h, int32_t chain, int64_t n_moves, int32_t epochs, int32_t batch, double lr,
@@ -522,55 +686,68 @@ int mc_train_surrogate(mc_handle* h, int32_t chain, int64_t n_moves, int32_t epo
         }
     }
     Net net;
-    if (!net.init(batch, lg.stream)) return mc_internal_fail(h, MC_E_OOM, "training workspace");
+    if (!net.init(batch, true, lg.stream)) return mc_internal_fail(h, MC_E_OOM, "training workspace");
+    // the moves of an epoch in their order, the loss of each of its steps and
+    // the outputs of the held-out moves: moved in one piece each, so that
+    // the steps follow one another without the host
+    const int64_t steps = n_tr / batch;
+    struct Held {
+        void* p = nullptr;
+        hipStream_t s;
+        ~Held() {
+            if (p) {
+                (void)hipStreamSynchronize(s);
+                (void)hipFree(p);
+            }
+        }
+    } held{nullptr, lg.stream};
+    const size_t order_bytes = round256(8 * (size_t)std::max(n_tr, n_val)), loss_bytes = round256(8 * (size_t)steps);
+    if (hipMalloc(&held.p, order_bytes + loss_bytes + 8 * (size_t)n_val) != hipSuccess)
+        return mc_internal_fail(h, MC_E_OOM, "training workspace");
+    int64_t* d_order = (int64_t*)held.p;
+    double* d_loss = (double*)((char*)held.p + order_bytes);
+    float* d_out = (float*)((char*)held.p + order_bytes + loss_bytes);
     if (!net.upload_params(p)) return mc_internal_fail(h, MC_E_DEVICE, "parameter upload");
     const double inv_lB = lg.lB > 0 ? 1.0 / lg.lB : 1.0;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     float c1 = 1.f, c2 = 1.f;
-    double last = 0.0;
+    std::vector<double> step_loss((size_t)steps);
     for (int e = 0; e < epochs; ++e) {
         std::shuffle(tr.begin(), tr.end(), rng);
-        double acc = 0.0;
-        for (int64_t b0 = 0; b0 < n_tr; b0 += batch) {
-            if (hipMemcpyAsync(net.idx, tr.data() + b0, 8 * (size_t)batch, hipMemcpyHostToDevice, net.s) != hipSuccess)
-                return mc_internal_fail(h, MC_E_DEVICE, "index upload");
-            hipLaunchKernelGGL(gather_kernel, dim3(batch), dim3(256), 0, net.s, lg.feat, lg.de, net.idx, batch, inv_lB,
-                               net.X, net.y);
-            net.forward(batch);
+        if (hipMemcpyAsync(d_order, tr.data(), 8 * (size_t)n_tr, hipMemcpyHostToDevice, net.s) != hipSuccess)
+            return mc_internal_fail(h, MC_E_DEVICE, "index upload");
+        for (int64_t k = 0; k < steps; ++k) {
             // b3 cancels in the difference of the two outputs: keep it at its value
-            net.outputs(batch, 0.f);
-            net.backward(batch);
+            net.gradient(batch, lg.feat, d_order + k * batch, lg.de, inv_lB, 0.f, d_loss + k);
             c1 *= b1;
             c2 *= b2;
             hipLaunchKernelGGL(adam_kernel, dim3((kNP + 255) / 256), dim3(256), 0, net.s, net.P, net.m, net.v, net.g, kNP,
-                               (float)lr, b1, b2, eps, 1.f - c1, 1.f - c2, net.Pw, net.W1b, net.W2b);
-            double l = 0.0;
-            if (hipMemcpyAsync(&l, net.loss, 8, hipMemcpyDeviceToHost, net.s) != hipSuccess ||
-                hipStreamSynchronize(net.s) != hipSuccess)
-                return mc_internal_fail(h, MC_E_DEVICE, "training step failed");
-            acc += l;
+                               (float)lr, b1, b2, eps, 1.f - c1, 1.f - c2, net.Pw, net.W1t, net.W2t, net.W2b);
         }
-        last = acc / (double)(n_tr / batch);
-        if (loss_out) loss_out[e] = last;
+        // (also before the next epoch's order replaces this one's)
+        if (hipMemcpyAsync(step_loss.data(), d_loss, 8 * (size_t)steps, hipMemcpyDeviceToHost, net.s) != hipSuccess ||
+            hipStreamSynchronize(net.s) != hipSuccess || hipGetLastError() != hipSuccess)
+            return mc_internal_fail(h, MC_E_DEVICE, "training step failed");
+        double acc = 0.0;
+        for (double l : step_loss) acc += l;
+        if (loss_out) loss_out[e] = acc / (double)steps;
     }
     // held-out loss and the stage-2 rejection rate the trained network gives
     // on the held-out moves: sum a1 (1 - a2) / sum a1 with a1 = min(1, e^-dEh)
     // and a2 = min(1, e^-(dE - dEh)) (stage 1 pass probability and stage 2
     // rejection probability of each move)
     double vl = 0.0, s_a1 = 0.0, s_rej = 0.0;
-    std::vector<float> outv(2 * (size_t)batch);
+    std::vector<float> outv(2 * (size_t)n_val);
+    if (hipMemcpyAsync(d_order, va.data(), 8 * (size_t)n_val, hipMemcpyHostToDevice, net.s) != hipSuccess)
+        return mc_internal_fail(h, MC_E_DEVICE, "index upload");
+    for (int64_t b0 = 0; b0 < n_val; b0 += batch) net.outputs(batch, lg.feat, d_order + b0, 0.f, d_out + 2 * b0);
+    if (hipMemcpyAsync(outv.data(), d_out, 4 * outv.size(), hipMemcpyDeviceToHost, net.s) != hipSuccess ||
+        hipStreamSynchronize(net.s) != hipSuccess || hipGetLastError() != hipSuccess)
+        return mc_internal_fail(h, MC_E_DEVICE, "evaluation failed");
     for (int64_t b0 = 0; b0 < n_val; b0 += batch) {
-        if (hipMemcpyAsync(net.idx, va.data() + b0, 8 * (size_t)batch, hipMemcpyHostToDevice, net.s) != hipSuccess)
-            return mc_internal_fail(h, MC_E_DEVICE, "index upload");
-        hipLaunchKernelGGL(gather_kernel, dim3(batch), dim3(256), 0, net.s, lg.feat, lg.de, net.idx, batch, inv_lB,
-                           net.X, net.y);
-        net.forward(batch);
-        net.outputs(batch, 0.f);
-        if (hipMemcpyAsync(outv.data(), net.out, 4 * outv.size(), hipMemcpyDeviceToHost, net.s) != hipSuccess ||
-            hipStreamSynchronize(net.s) != hipSuccess)
-            return mc_internal_fail(h, MC_E_DEVICE, "evaluation failed");
+        const float* o = outv.data() + 2 * b0;
         for (int b = 0; b < batch; ++b) {
-            const double dEh = lg.lB * ((double)outv[batch + b] - (double)outv[b]);
+            const double dEh = lg.lB * ((double)o[batch + b] - (double)o[b]);
             const double dE = de[va[b0 + b]];
             const double r = dEh - dE;
             vl += (r * inv_lB) * (r * inv_lB);
@@ -586,7 +763,6 @@ int mc_train_surrogate(mc_handle* h, int32_t chain, int64_t n_moves, int32_t epo
     if (hipMemcpy(pf.data(), net.Pw, 4 * kNP, hipMemcpyDeviceToHost) != hipSuccess)
         return mc_internal_fail(h, MC_E_DEVICE, "parameter download");
     for (int k = 0; k < kNP; ++k) params_out[k] = pf[k];
-    (void)last;
     return MC_OK;
 }
 
