@@ -18,6 +18,58 @@ struct EnergyAux {
     unsigned long long n_resum;
 };
 
+// Stats slots written by the sweep kernel.
+enum { ST_MOVES = 0, ST_ACC, ST_WALL, ST_OVERLAP, ST_METRO, ST_ITERS, ST_EARLY,
+       ST_DA_MOVES, ST_DA_CONFLICTS, ST_DA_S1REJ, ST_DA_S1PASS, ST_DA_S2REJ, ST_N };
+
+// What the host reads of a chain between launches, and where it lies.
+struct ChainReport {
+    int32_t abort, pad;
+    double e_state;
+    EnergyAux aux;
+    DAState da;
+    unsigned long long stats[ST_N];
+};
+constexpr size_t kReportHead = 512;  // positions follow the report from here
+static_assert(sizeof(ChainReport) <= kReportHead, "report layout");
+struct ReportSource {
+    const int* abort;
+    const double* e_state;
+    const EnergyAux* aux;
+    const DAState* da;
+    const unsigned long long* stats;
+};
+
+// The report to r and count values of the packed positions to xyz, both
+// pinned host memory, four values a thread (xyz has room for whole fours).
+// Bound: one launch and one wait, 9 us in all; a copy per item into pageable
+// memory took 10 us each.
+template <typename T, typename T4>
+__global__ void __launch_bounds__(256)
+report_kernel(ReportSource s, ChainReport* __restrict__ r, const T4* __restrict__ pos, int count, T* __restrict__ xyz)
+{
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.x == 0) {
+        if (t < ST_N) r->stats[t] = s.stats[t];
+        if (t == 64) {
+            r->abort = *s.abort;
+            r->e_state = *s.e_state;
+        }
+        if (t == 128) r->aux = *s.aux;
+        if (t == 192) r->da = *s.da;
+    }
+    if (4 * t >= count) return;
+    T v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int e = min(4 * t + k, count - 1);
+        const T* p = reinterpret_cast<const T*>(pos + e / 3);
+        v[k] = p[e % 3];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) xyz[4 * t + k] = v[k];
+}
+
 // Work item of a batched auxiliary launch: chain index and the block's index
 // inside that chain.
 struct BlockItem {

@@ -34,9 +34,6 @@ namespace {
 
 thread_local std::string g_create_error = "no error";
 
-// Stats slots written by the sweep kernel.
-enum { ST_MOVES = 0, ST_ACC, ST_WALL, ST_OVERLAP, ST_METRO, ST_ITERS, ST_EARLY,
-       ST_DA_MOVES, ST_DA_CONFLICTS, ST_DA_S1REJ, ST_DA_S1PASS, ST_DA_S2REJ, ST_N };
 
 constexpr int64_t kMaxLaunchSweeps = 4096;
 static_assert(kDaParams == MC_DA_NPARAM, "network size differs from the header");
@@ -202,6 +199,10 @@ struct mc_handle {
     ReducePart* d_rparts = nullptr;  // [r_blocks]
     ReduceCtl* d_rctl = nullptr;
     int r_blocks = 0;
+    // pinned host memory the small reads of a chain arrive in: a ChainReport,
+    // then the positions of chains of up to report_ions ions
+    void* report = nullptr;
+    int report_ions = 0;
 };
 
 namespace {
@@ -261,8 +262,21 @@ void free_all(mc_handle* h) {
     if (h->d_rctl) (void)hipFree(h->d_rctl);
     h->d_rparts = nullptr;
     h->d_rctl = nullptr;
+    if (h->report) (void)hipHostFree(h->report);
+    h->report = nullptr;
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     h->stream = nullptr;
+}
+
+// Judges the device abort word; marks the handle failed on error.
+int abort_check(mc_handle* h, int ab) {
+    if (ab != 0) {
+        return fail(h, ab == MC_E_TIMEOUT ? MC_E_TIMEOUT : ab == MC_E_STATE ? MC_E_STATE : MC_E_DEVICE,
+                    ab == MC_E_TIMEOUT ? "a device-side wait timed out (chain state is invalid)"
+                    : ab == MC_E_STATE ? "a group record or position was not the one expected (chain state is invalid)"
+                                       : "device reported an error");
+    }
+    return MC_OK;
 }
 
 // Checks the device abort word and the stream; marks the handle failed on error.
@@ -272,13 +286,7 @@ int sync_check(mc_handle* h) {
     if (e != hipSuccess) return fail(h, MC_E_DEVICE, std::string("stream: ") + hipGetErrorString(e));
     int ab = 0;
     HIPCHECK(h, hipMemcpy(&ab, h->abort_flag, sizeof(int), hipMemcpyDeviceToHost));
-    if (ab != 0) {
-        return fail(h, ab == MC_E_TIMEOUT ? MC_E_TIMEOUT : ab == MC_E_STATE ? MC_E_STATE : MC_E_DEVICE,
-                    ab == MC_E_TIMEOUT ? "a device-side wait timed out (chain state is invalid)"
-                    : ab == MC_E_STATE ? "a group record or position was not the one expected (chain state is invalid)"
-                                       : "device reported an error");
-    }
-    return MC_OK;
+    return abort_check(h, ab);
 }
 
 bool is_finite(double v) { return std::isfinite(v); }
@@ -858,6 +866,8 @@ int sweep_all(mc_handle* h, int64_t n_sweeps, uint64_t seed, LaunchFn launch = l
     return MC_OK;
 }
 
+constexpr int kReportIons = 16384;
+
 // Builds a handle from validated chain specs.
 int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options& opt, mc_handle** out) {
     mc_handle* h = new (std::nothrow) mc_handle();
@@ -1015,6 +1025,17 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
         }
     }
     if ((rc = dalloc(h, &h->arena, plan.size))) return bail(rc);
+    // Positions of chains above kReportIons ions are copied as they lie, so
+    // that a handle pins at most 384 KB (a read of 16384 ions takes 31 us
+    // packed, 50 to 65 copied; of 300 ions 15 against 35; above, a read is a
+    // small part of the sweeps between two of them).
+    h->report_ions = std::min(n_most, kReportIons);
+    if (hipHostMalloc(&h->report, kReportHead + (h->fp64 ? sizeof(double) : sizeof(float)) * (3 * (size_t)h->report_ions + 3),
+                      hipHostMallocDefault) != hipSuccess) {
+        h->report = nullptr;
+        h->err = "pinned host memory";
+        return bail(MC_E_OOM);
+    }
     plan.assign(h->arena);
     // zero everything once (the handle's stream is non-blocking: drain it
     // before the synchronous uploads below)
@@ -1189,18 +1210,41 @@ Chain* get_chain(mc_handle* h, int32_t c) {
     return &h->chains[c];
 }
 
+// Reads a chain's small state (and, with xyz, its positions) off the device:
+// one kernel on the handle's stream stores it in the handle's pinned memory,
+// one wait, then the abort word is judged.  *out is valid until the next read.
+int read_report(mc_handle* h, const Chain& c, const ChainReport** out, const void** xyz = nullptr) {
+    if (h->failed) return fail(h, MC_E_STATE, "handle is in a failed state: " + h->err);
+    ChainReport* r = (ChainReport*)h->report;
+    void* to = (char*)h->report + kReportHead;
+    const int parity = (int)((h->sweeps - 1) & 1);
+    const ReportSource src{h->abort_flag, c.e_state, c.aux, c.da, c.stats};
+    const unsigned blocks = xyz ? (unsigned)((3 * c.n + 4 * 256 - 1) / (4 * 256)) : 1;
+    if (h->fp64)
+        hipLaunchKernelGGL((report_kernel<double, double4>), dim3(blocks), dim3(256), 0, h->stream, src, r,
+                           (const double4*)c.pos + (size_t)parity * c.npad, xyz ? 3 * c.n : 0, (double*)to);
+    else
+        hipLaunchKernelGGL((report_kernel<float, float4>), dim3(blocks), dim3(256), 0, h->stream, src, r,
+                           (const float4*)c.pos + (size_t)parity * c.npad, xyz ? 3 * c.n : 0, (float*)to);
+    HIPCHECK(h, hipGetLastError());
+    const hipError_t e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) return fail(h, MC_E_DEVICE, std::string("stream: ") + hipGetErrorString(e));
+    *out = r;
+    if (xyz) *xyz = to;
+    return abort_check(h, r->abort);
+}
+
 int chain_energy(mc_handle* h, int32_t ci, double* e_running, double* e_exact) {
     Chain* c = get_chain(h, ci);
     if (!c || !e_running) return h ? fail(h, MC_E_ARG, "bad chain index or null output") : MC_E_ARG;
-    int rc = sync_check(h);
+    const ChainReport* r = nullptr;
+    int rc = read_report(h, *c, &r);
     if (rc) return rc;
-    HIPCHECK(h, hipMemcpy(e_running, c->e_state, sizeof(double), hipMemcpyDeviceToHost));
+    *e_running = r->e_state;
     if (e_exact) {
         if ((rc = launch_energy(h, 0, 0))) return rc;
-        if ((rc = sync_check(h))) return rc;
-        EnergyAux a;
-        HIPCHECK(h, hipMemcpy(&a, c->aux, sizeof(EnergyAux), hipMemcpyDeviceToHost));
-        *e_exact = a.e_resum;
+        if ((rc = read_report(h, *c, &r))) return rc;
+        *e_exact = r->aux.e_resum;
     }
     return MC_OK;
 }
@@ -1255,6 +1299,17 @@ int chain_species(const mc_handle* h, int32_t ci, int32_t* ntypes, double* q, do
 int chain_positions(mc_handle* h, int32_t ci, double* xyz) {
     Chain* c = get_chain(h, ci);
     if (!c || !xyz) return h ? fail(h, MC_E_ARG, "bad chain index or null output") : MC_E_ARG;
+    if (c->n <= h->report_ions) {
+        const ChainReport* r = nullptr;
+        const void* from = nullptr;
+        const int rc = read_report(h, *c, &r, &from);
+        if (rc) return rc;
+        if (h->fp64)
+            std::memcpy(xyz, from, sizeof(double) * 3 * c->n);
+        else
+            for (int i = 0; i < 3 * c->n; ++i) xyz[i] = ((const float*)from)[i];
+        return MC_OK;
+    }
     int rc = sync_check(h);
     if (rc) return rc;
     const int parity = (int)((h->sweeps - 1) & 1);
@@ -1305,12 +1360,12 @@ int chain_energy_series(mc_handle* h, int32_t ci, int64_t n, double* e) {
 int chain_stats(mc_handle* h, int32_t ci, mc_stats* out) {
     Chain* c = get_chain(h, ci);
     if (!c || !out) return h ? fail(h, MC_E_ARG, "bad chain index or null output") : MC_E_ARG;
-    int rc = sync_check(h);
+    const ChainReport* r = nullptr;
+    int rc = read_report(h, *c, &r);
     if (rc) return rc;
-    unsigned long long st[ST_N];
-    EnergyAux a;
-    HIPCHECK(h, hipMemcpy(st, c->stats, sizeof(st), hipMemcpyDeviceToHost));
-    HIPCHECK(h, hipMemcpy(&a, c->aux, sizeof(a), hipMemcpyDeviceToHost));
+    const unsigned long long* st = r->stats;
+    const EnergyAux& a = r->aux;
+    const DAState& ds = r->da;
     std::memset(out, 0, sizeof(*out));
     out->sweeps = h->sweeps;
     out->moves = (int64_t)st[ST_MOVES];
@@ -1326,8 +1381,6 @@ int chain_stats(mc_handle* h, int32_t ci, mc_stats* out) {
     out->band = c->band;
     out->waves = h->waves;
     out->workgroups = c->wg;
-    DAState ds;
-    HIPCHECK(h, hipMemcpy(&ds, c->da, sizeof(ds), hipMemcpyDeviceToHost));
     out->da_active = ds.active && c->da_w != nullptr ? 1 : 0;
     out->da_moves = (int64_t)st[ST_DA_MOVES];
     out->da_conflicts = (int64_t)st[ST_DA_CONFLICTS];

@@ -439,18 +439,19 @@ struct Net {
     hipStream_t s = nullptr;
 
     // every buffer of a batch of B moves (the optimizer's moments only when
-    // training, the staged histograms only when not), each obtained from
-    // take(&pointer, bytes)
+    // training; the staged targets and histograms only when not, beside P, so
+    // that a pass's inputs go up in one copy), each obtained from
+    // take(&pointer, bytes); the loss lies behind g, to come back with it
     template <typename Take>
     static bool layout(Net& n, int B, bool train, Take&& take) {
         const size_t R = 2 * (size_t)B;
-        return take(&n.P, 4 * kNP) && take(&n.Pw, 4 * kNP) && (!train || (take(&n.m, 4 * kNP) && take(&n.v, 4 * kNP))) &&
-               take(&n.g, 4 * kNP) && take(&n.W1t, 2 * kIn * kHid) && take(&n.W2t, 2 * kHid * kHid) &&
+        return take(&n.P, 4 * kNP) && (train || (take(&n.y, 4 * (size_t)B) && take(&n.feat, (size_t)B * 2 * kIn))) &&
+               take(&n.Pw, 4 * kNP) && (!train || (take(&n.m, 4 * kNP) && take(&n.v, 4 * kNP))) &&
+               take(&n.g, 4 * kNP) && take(&n.loss, 8) && take(&n.W1t, 2 * kIn * kHid) && take(&n.W2t, 2 * kHid * kHid) &&
                take(&n.W2b, 2 * kHid * kHid) && take(&n.X, 2 * R * kIn) && take(&n.H1, 2 * R * kHid) &&
                take(&n.H2, 2 * R * kHid) && take(&n.dZ2b, 2 * R * kHid) && take(&n.dZ1b, 2 * R * kHid) &&
                take(&n.out, 4 * R) && take(&n.dout, 4 * R) && take(&n.res, 4 * (size_t)B) &&
-               take(&n.dZ2, 4 * R * kHid) && take(&n.dZ1, 4 * R * kHid) && take(&n.y, 4 * (size_t)B) &&
-               take(&n.loss, 8) && (train || take(&n.feat, (size_t)B * 2 * kIn));
+               take(&n.dZ2, 4 * R * kHid) && take(&n.dZ1, 4 * R * kHid);
     }
     // bytes of the layout, each buffer rounded up to 256
     static size_t bytes(int B, bool train) {
@@ -484,8 +485,10 @@ struct Net {
         if (s) (void)hipStreamSynchronize(s);
         (void)hipFree(own);
     }
-    bool upload_params(const std::vector<float>& p) {
-        if (hipMemcpy(P, p.data(), 4 * kNP, hipMemcpyHostToDevice) != hipSuccess) return false;
+    // P from host memory (and, of a gradient pass, the staged inputs behind
+    // it: `bytes` in all), and the working copies
+    bool upload_params(const void* p, size_t bytes = 4 * kNP) {
+        if (hipMemcpy(P, p, bytes, hipMemcpyHostToDevice) != hipSuccess) return false;
         if (m && hipMemset(m, 0, 4 * kNP) != hipSuccess) return false;
         if (v && hipMemset(v, 0, 4 * kNP) != hipSuccess) return false;
         hipLaunchKernelGGL(refresh_kernel, dim3((kNP + 255) / 256), dim3(256), 0, s, P, kNP, Pw, W1t, W2t, W2b);
@@ -576,14 +579,14 @@ unsigned char* device_scratch() {
 // p the same in float), on the null stream.
 int gradient_pass(Net& net, int batch, const uint8_t* feats, const double* target, const double* params,
                   const std::vector<float>& p, double* loss, double* grad, std::string& err) {
-    if (!net.upload_params(p)) {
-        err = "parameter upload failed";
-        return MC_E_DEVICE;
-    }
-    std::vector<float> y(batch);
+    // P, y and feat as they lie on the device, in one copy
+    const size_t y_at = (unsigned char*)net.y - (unsigned char*)net.P, f_at = net.feat - (unsigned char*)net.P;
+    std::vector<unsigned char> up(f_at + (size_t)batch * 2 * kIn);
+    std::memcpy(up.data(), p.data(), 4 * kNP);
+    float* y = (float*)(up.data() + y_at);
     for (int b = 0; b < batch; ++b) y[b] = (float)target[b];
-    if (hipMemcpy(net.feat, feats, (size_t)batch * 2 * kIn, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(net.y, y.data(), 4 * (size_t)batch, hipMemcpyHostToDevice) != hipSuccess) {
+    std::memcpy(up.data() + f_at, feats, (size_t)batch * 2 * kIn);
+    if (!net.upload_params(up.data(), up.size())) {
         err = "input upload failed";
         return MC_E_DEVICE;
     }
@@ -594,13 +597,15 @@ int gradient_pass(Net& net, int batch, const uint8_t* feats, const double* targe
         err = "the gradient pass failed on the device";
         return MC_E_DEVICE;
     }
-    std::vector<float> g(kNP);
-    double l = 0.0;
-    if (hipMemcpy(g.data(), net.g, 4 * kNP, hipMemcpyDeviceToHost) != hipSuccess ||
-        hipMemcpy(&l, net.loss, 8, hipMemcpyDeviceToHost) != hipSuccess) {
+    const size_t l_at = (unsigned char*)net.loss - (unsigned char*)net.g;
+    std::vector<unsigned char> down(l_at + sizeof(double));
+    if (hipMemcpy(down.data(), net.g, down.size(), hipMemcpyDeviceToHost) != hipSuccess) {
         err = "output download failed";
         return MC_E_DEVICE;
     }
+    const float* g = (const float*)down.data();
+    double l;
+    std::memcpy(&l, down.data() + l_at, sizeof(l));
     if (loss) *loss = l;
     if (grad)
         for (int k = 0; k < kNP; ++k) grad[k] = g[k];
@@ -707,7 +712,7 @@ int mc_train_surrogate(mc_handle* h, int32_t chain, int64_t n_moves, int32_t epo
     int64_t* d_order = (int64_t*)held.p;
     double* d_loss = (double*)((char*)held.p + order_bytes);
     float* d_out = (float*)((char*)held.p + order_bytes + loss_bytes);
-    if (!net.upload_params(p)) return mc_internal_fail(h, MC_E_DEVICE, "parameter upload");
+    if (!net.upload_params(p.data())) return mc_internal_fail(h, MC_E_DEVICE, "parameter upload");
     const double inv_lB = lg.lB > 0 ? 1.0 / lg.lB : 1.0;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     float c1 = 1.f, c2 = 1.f;
