@@ -77,18 +77,6 @@ struct BlockItem {
     int32_t part;
 };
 
-// 1 / sqrt(d2) in double from the hardware estimate (v_rsq_f64, about 26
-// bits) and one third-order step: with e = 1 - d2 y^2 (formed with a fused
-// multiply-add, so its rounding does not matter), y (1 + e / 2 + 3 e^2 / 8)
-// is off by e^3, far below a rounding; the result is within one unit in the
-// last place, as a rounded sqrt followed by a rounded division is.  Six
-// instructions instead of the 28 of those two.  NaN for d2 = 0 or infinity.
-__device__ __forceinline__ double rsqrt_refined(double d2) {
-    const double y = __builtin_amdgcn_rsq(d2);
-    const double e = __builtin_fma(-(d2 * y), y, 1.0);
-    return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
-}
-
 // Blocks per pair of super-rows of the re-sum (below) for a chain of nb
 // groups in a handle whose chains have total_pairs such pairs: enough blocks
 // for eight a CU (2048 in all), while every wave keeps at least two tiles.
@@ -175,7 +163,7 @@ energy_partial_kernel(const ChainDesc* __restrict__ chains, const BlockItem* __r
                     }
                 }
             };
-            auto fast = [](double d2) { return rsqrt_refined(d2); };
+            auto fast = [](double d2) { return rsqrt_step(d2, __builtin_amdgcn_rsq(d2)); };
             auto plain = [](double d2) { return 1.0 / __builtin_sqrt(d2); };
             if (t > row1)
                 terms(std::false_type{}, fast);
