@@ -1002,6 +1002,7 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
         plan.add(&c.wall_a, sizeof(double) * c.npad);
         plan.add(&c.d_type, sizeof(int32_t) * c.npad);
         plan.add(&c.rec, sizeof(GroupRec) * kRing);
+        plan.add(&c.da, sizeof(DAState));  // (pos to here: uploaded in one piece)
         plan.add(&c.stats, sizeof(unsigned long long) * ST_N);
         plan.add(&c.clk, sizeof(unsigned long long) * 2);
         plan.add(&c.e_partial, sizeof(double) * energy_pairs(c.nb) * c.e_split);
@@ -1018,7 +1019,6 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
             plan.add(&c.rdf_rank, sizeof(int32_t) * c.npad);
             plan.add(&c.rdf_sorted, t4 * c.npad);
         }
-        plan.add(&c.da, sizeof(DAState));
         if (c.trace_cap > 0) {
             plan.add(&c.trace_acc, (size_t)c.trace_cap);
             plan.add(&c.trace_de, sizeof(double) * c.trace_cap);
@@ -1055,8 +1055,10 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
         // positions carry the version tag of the sweep that produced them;
         // the initial state is the result of virtual sweeps -2 (parity 0)
         // and -1 (parity 1)
-        std::vector<char> hpos(2 * t4 * c.npad), hhalf(t1 * c.npad), hq(t1 * c.npad);
-        std::vector<double> hwall(c.npad, 0.0);
+        std::vector<char> img((char*)(c.da + 1) - (char*)c.pos);  // as it lies in the arena
+        auto at = [&](const void* p) { return img.data() + ((const char*)p - (const char*)c.pos); };
+        char *hpos = at(c.pos), *hhalf = at(c.half), *hq = at(c.charge);
+        double* hwall = (double*)at(c.wall_a);
         for (int i = 0; i < c.npad; ++i) {
             double x, y, z, qq, hh;
             if (i < c.n) {
@@ -1094,18 +1096,20 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
                 std::memcpy(&hq[t1 * i], &qf, t1);
             }
         }
-        std::vector<GroupRec> hrec(kRing);
+        GroupRec* hrec = (GroupRec*)at(c.rec);
         for (int q = 0; q < kRing; ++q) {
             const int64_t g = (int64_t)q - kRing;  // virtual groups -kRing..-1: decided, nothing accepted
             hrec[(size_t)(g & (kRing - 1))] = GroupRec{(uint32_t)(g + 1), 0u, 0ull};
         }
         hipError_t e = hipSuccess;
-        if ((e = hipMemcpy(c.pos, hpos.data(), hpos.size(), hipMemcpyHostToDevice)) != hipSuccess ||
-            (e = hipMemcpy(c.half, hhalf.data(), hhalf.size(), hipMemcpyHostToDevice)) != hipSuccess ||
-            (e = hipMemcpy(c.charge, hq.data(), hq.size(), hipMemcpyHostToDevice)) != hipSuccess ||
-            (e = hipMemcpy(c.wall_a, hwall.data(), sizeof(double) * c.npad, hipMemcpyHostToDevice)) != hipSuccess ||
-            (e = hipMemcpy(c.d_type, c.type.data(), sizeof(int32_t) * c.npad, hipMemcpyHostToDevice)) != hipSuccess ||
-            (e = hipMemcpy(c.rec, hrec.data(), sizeof(GroupRec) * kRing, hipMemcpyHostToDevice)) != hipSuccess) {
+        std::memcpy(at(c.d_type), c.type.data(), sizeof(int32_t) * c.npad);
+        DAState da{};
+        da.fallback_sweep = -1;
+        da.ref_rate = -1.0;
+        da.last_rate = -1.0;
+        da.min_count = 64;
+        std::memcpy(at(c.da), &da, sizeof(da));
+        if ((e = hipMemcpy(c.pos, img.data(), img.size(), hipMemcpyHostToDevice)) != hipSuccess) {
             h->err = std::string("upload failed: ") + hipGetErrorString(e);
             return bail(MC_E_DEVICE);
         }
@@ -1129,15 +1133,6 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
     }
     for (Chain& c : h->chains) {
         if ((rc = grow_buffer(h, &c.e_series, &c.e_capacity, 1024, false))) return bail(rc);
-        DAState z{};
-        z.fallback_sweep = -1;
-        z.ref_rate = -1.0;
-        z.last_rate = -1.0;
-        z.min_count = 64;
-        if (hipMemcpy(c.da, &z, sizeof(z), hipMemcpyHostToDevice) != hipSuccess) {
-            h->err = "upload failed";
-            return bail(MC_E_DEVICE);
-        }
         if (opt.log_moves > 0) {
             c.log_cap = opt.log_moves;
             if ((rc = dalloc(h, &c.log_feat, sizeof(uint32_t) * 64 * (size_t)c.log_cap)) ||
