@@ -99,8 +99,9 @@ typedef struct mc_options {
     int32_t waves;          /* waves per workgroup (4 or 8), 0 = automatic:
                                8 for float chains of at least 3 groups of 64
                                per compute unit in all (one chain: N >= 49089
-                               on 256 CUs) without move logging, else 4.
-                               Delayed acceptance needs 4                   */
+                               on 256 CUs) without move logging and for
+                               double chains until a surrogate is installed,
+                               else 4.  Delayed acceptance needs 4          */
     int32_t workgroups;     /* workgroups serving the chain, 0 = automatic         */
     int64_t trace_moves;    /* record accept bit and dE of the first this many
                                moves of the chain (global move index
