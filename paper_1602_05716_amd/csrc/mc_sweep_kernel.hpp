@@ -603,7 +603,11 @@ __device__ __forceinline__ void chain_step(SweepShared<T, M, DA>& sh, const Chai
         const bool reject_sure = !can || s1_rej || ov_sure != 0 || (ovo & ovt) != 0;
         const bool accept_sure = !reject_sure && ov_flip == 0 && e_hi < thr_eff - margin;
         const bool sure = reject_sure || accept_sure || (ov_flip == 0 && e_lo >= thr_eff + margin);
-        if (__ballot(!sure) == 0ull) {
+        // Not in a chain so short that a group whose mask is still unknown
+        // here (the newest LC of the band) has this group's ions in its own band: it may
+        // still be reading the positions, two sweeps old, that publishing
+        // overwrites.
+        if (nb > band + (band < LC ? band : LC) && __ballot(!sure) == 0ull) {
             early = true;
             acc = __ballot(accept_sure);
             dec = accept_sure;
