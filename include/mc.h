@@ -95,7 +95,9 @@ typedef struct mc_options {
                                chains with both.  Automatic on eight waves: 1
                                for a float chain whose workgroups serve at
                                least four of its groups a sweep in the
-                               schedule planned at creation                    */
+                               schedule planned at creation.  Automatic for
+                               a double chain without a surrogate or a move
+                               log: 1 up to 8 groups, 2 up to 32               */
     int32_t waves;          /* waves per workgroup (4 or 8), 0 = automatic:
                                8 for float chains of at least 3 groups of 64
                                per compute unit in all (one chain: N >= 49089

@@ -10,6 +10,25 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("n,band", [(64, 0), (128, 1), (512, 1), (514, 2), (2048, 2), (2050, 4)])
+def test_automatic_band_of_double_chains(oracle, n, band):
+    """The automatic band by size, the oracle's decisions on it, and the
+    widest the two-stage kernel holds once a surrogate is installed."""
+    from paper_1602_05716_amd import inputs, mc, surrogate
+    sy = inputs.electrolyte(n // 2, n // 2, 1.0, -1.0, 1.0, 1.0, 0.04, 0.7)
+    sy.xyz = inputs.random_start(sy, 18)
+    with mc.Chain(sy.xyz, sy.q, sy.sigma, sy.R, sy.lB, precision="fp64", max_disp=0.8, resum_every=0,
+                  trace_moves=2 * n) as ch:
+        assert ch.stats()["band"] == band
+        ch.sweep(2, 12)
+        acc, de = ch.trace(2 * n)
+        ch.set_surrogate(surrogate.truncated_coulomb_params(2.0), 0.5, True)
+        assert ch.stats()["band"] == min(3, (n + 63) // 64 - 1)
+    r = oracle.Chain(sy.xyz, sy.q, sy.sigma, sy.R, sy.lB, 1.6, seed=12).run(2, trace=2 * n)
+    assert np.array_equal(acc, r["acc"])
+    assert np.max(np.abs(de - r["dE"]) / np.maximum(np.abs(r["dE"]), 1.0)) < 1e-10
+
+
 @pytest.mark.parametrize("n,per_ion", [(50, False), (130, True), (1000, False)])
 def test_automatic_waves_and_surrogate(n, per_ion):
     from paper_1602_05716_amd import inputs, mc, surrogate
