@@ -2146,6 +2146,8 @@ int mc_set_surrogate(mc_handle* h, int32_t chain, const double* params, double r
             return fail(h, MC_E_ARG, "more chains than co-resident workgroups of the delayed-acceptance kernel");
         h->da_kernel = true;
         h->waves = 4;  // (a double handle's automatic eight end here)
+        // the kernel serves every chain of the handle, surrogate or not
+        for (Chain& c : h->chains) c.band = std::min(c.band, kDaMaxBand);
         std::vector<int> wg;
         WgLists lists;
         plan_schedule(h, wg, lists);
