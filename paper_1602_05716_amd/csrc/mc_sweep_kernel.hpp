@@ -48,6 +48,7 @@
 #pragma once
 
 #include <type_traits>
+#include <utility>
 
 #include "mc_device.hpp"
 
@@ -265,6 +266,13 @@ constexpr int kDecidedSlice = (sizeof(T) == 4 && M == 8 && !DA) ? 64 : kGroup / 
 // every two microseconds, far slower than a tile takes to compute.
 constexpr int kPatientDistance = 6;
 
+// Decided groups this close before the last one the target waits for are taken
+// one at a time.
+constexpr int kQuadMargin = 12;
+// Entries of a wave's ring of near partners: one partner adds up to 64, and
+// the ring is emptied by 64 as soon as it holds that many.
+constexpr int kNearRing = 128;
+
 template <typename T, int M, bool DA = false>
 struct SweepShared {
     using T4 = typename Prec<T>::T4;
@@ -275,8 +283,11 @@ struct SweepShared {
     using SB = typename SliceBits<P>::type;
     // per compute wave: staging of the current partner slice {x, y, z, q}
     // (a decided tile of PD > P partners continues in st_old2 / st_half2)
-    T4 st_old[M][P];
-    T4 st_new[M][P];
+    // (the float delayed-acceptance kernels stage four decided slices at once)
+    static constexpr int SW = sizeof(T) == 4 && DA ? 4 * P : 2 * P;
+    T4 st[M][SW];
+    __device__ T4* old_of(int w) { return st[w]; }
+    __device__ T4* new_of(int w) { return st[w] + P; }
     T st_half[M][P];
     // hand-off from the compute waves to the chain wave (one target at a time)
     double part_s[M][kGroup];   // partial sums over each wave's partners
@@ -308,23 +319,24 @@ struct SweepShared {
     // delayed acceptance: per mover, byte histograms of neighbour distances at
     // the old position (bytes 0..127) and at the trial position (128..255),
     // each like-charged bins 0..63 then unlike-charged; conflict ballots of
-    // the waves; the surrogate's dEh; partial sums of the network's last layer
+    // the waves; the surrogate's dEh
     uint32_t hist[DA ? kGroup : 1][DA ? 65 : 1];   // rows padded to 65 words (bank-conflict free)
     uint64_t part_conf[DA ? M : 1];
     double deh[DA ? kGroup : 1];
-    float part_out[DA ? M : 1][2][DA ? kGroup : 1];
+    float net_out[DA ? 2 * kGroup : 1];       // network output of each (position, mover)
+    alignas(16) float bias[DA ? 3 : 1][DA ? kDaHid : 4];  // b1, b2, w3 and ...
+    float bias3;                                          // ... b3; loaded once per launch
     // the network's two matrices, transposed ([hidden unit][input]), as
     // bfloat16, rows padded to 132 values (8-byte reads free of bank
     // conflicts); loaded once per launch
     static constexpr bool kWtsLds = DA && sizeof(T) == 4;  // (the double kernel reads them from memory)
     uint16_t wts[kWtsLds ? 2 * kDaHid : 1][kWtsLds ? kDaIn + 4 : 1];
-    // bfloat16 hidden activations [mover][position][unit] of the network, in
-    // the space of c_own and c_b (free between the chain wave's release and
-    // the next hand-off)
-    __device__ uint16_t* h1() { return reinterpret_cast<uint16_t*>(&c_own[0][0]); }
     // placed last, so that the fields above keep their offsets
     T4 st_old2[M][PD > P ? PD - P : 1];
     T st_half2[M][PD > P ? PD - P : 1];
+    // delayed acceptance: per wave, a ring of partners found near a mover
+    // {x, y, z, mover lane + 64 if unlike}, binned 64 at a time
+    T4 near[DA ? M : 1][DA ? kNearRing : 1];
 };
 
 // The 64-bit word of overlap bits that the waves' slices tile.
@@ -436,6 +448,7 @@ struct MoverInputs {
     bool wall;
     double thr;
     double lq;
+    double log_u2;  // two-stage test: log of the second stage's uniform
 };
 
 template <typename T>
@@ -559,9 +572,8 @@ __device__ __forceinline__ void chain_step(SweepShared<T, M, DA>& sh, const Chai
             da_lane = true;
             deh = sh.deh[lane];
             if (deh <= 0.0 || deh < thr) {
-                const uint4 w2 = move_words(cd.seed, cd.chain_id, (uint32_t)s, (uint32_t)ion, 2u);
                 shift = deh;
-                thr_eff = deh - log(accept_uniform(w2.x));
+                thr_eff = deh - mi.log_u2;
             } else {
                 s1_rej = true;
                 shift = thr_eff = -1.0e300;
@@ -813,42 +825,71 @@ __device__ __forceinline__ double d2_exact(double ax, double ay, double az, doub
 // Adds a neighbour at squared distance d2 to byte bin (pos, like/unlike, k)
 // of mover `lane`'s histogram (four byte counters per LDS word).
 template <typename SH>
-__device__ __forceinline__ void da_hist_add(SH& sh, const ChainDesc& cd, int lane, int pos, bool unlike, double d2) {
+__device__ __forceinline__ void da_hist_add(SH& sh, const ChainDesc& cd, float inv_dr, int lane, int pos, bool unlike,
+                                            double d2) {
     if (!(d2 < cd.da_rc * cd.da_rc)) return;
-    const int k = (int)__builtin_floor(__builtin_sqrt(d2) / cd.da_dr);
+    // floor(sqrt(d2) / dr): in float (off by less than 1e-4 up to bin 64)
+    // unless that lies next to a bin's edge
+    const float v = __builtin_amdgcn_sqrtf((float)d2) * inv_dr;
+    const int k = __builtin_fabsf(v - __builtin_rintf(v)) > 1e-3f
+                      ? (int)v
+                      : (int)__builtin_floor(__builtin_sqrt(d2) / cd.da_dr);
     if (k >= kDaBins) return;
     const int byte = pos * kDaIn + (unlike ? kDaBins : 0) + k;
     atomicAdd(&sh.hist[lane][byte >> 2], 1u << (8 * (byte & 3)));
 }
 
-__device__ __forceinline__ float bf16_round(float v) {
-    uint32_t b = __builtin_bit_cast(uint32_t, v);
-    b += 0x7FFFu + ((b >> 16) & 1u);
-    return __builtin_bit_cast(float, b & 0xFFFF0000u);
-}
-
-// Delayed-acceptance stage of one target group, run by all 4 waves between
-// the chain wave's release of the hand-off buffer and the next hand-off:
-// logs the movers' histograms, evaluates the network eps at both positions
-// of every mover and leaves dEh = l_B (eps(trial) - eps(old)) in sh.deh, then
-// clears the histograms.  Both hidden layers run on the matrix cores as
-// [128 rows x 128] x [128 x 128] bfloat16 products with float sums
-// (v_mfma_f32_32x32x8bf16_1k): row r = 64 * position + mover, wave w takes
-// rows 32 w .. 32 w + 31 and all four 32-column tiles (the matrices are
-// read from LDS, where the kernel put them at its start); lane l holds
-// A[l % 32][4 (l / 32) + v], B[4 (l / 32) + v][l % 32] and
-// D[8 (i / 4) + 4 (l / 32) + i % 4][l % 32].  Hidden activations are
-// rounded to bfloat16.
+// Delayed-acceptance stage of one target group, run by all 4 waves after the
+// last partner tile: logs the movers' histograms, evaluates the network eps
+// at both positions of every mover, leaves dEh = l_B (eps(trial) - eps(old))
+// in sh.deh and clears the histograms.  Both hidden layers run on the matrix
+// cores (v_mfma_f32_32x32x8bf16_1k) as [128 units x 128] x [128 x 128 rows],
+// row r = 64 * position + mover, bfloat16 values with float sums: wave w
+// takes rows 32 w .. 32 w + 31 and all four 32-unit tiles.  Lane l gives
+// A[l % 32][4 (l / 32) + v] (weights, from LDS where the kernel put them at
+// its start) and B[4 (l / 32) + v][l % 32], and gets D[8 (i / 4) + 4 (l / 32)
+// + i % 4][l % 32]: what it gets of a layer is what it gives of the next, so
+// nothing passes through LDS between the layers, and a row's last sum is
+// all but four additions within a lane.  Hidden activations are rounded to
+// bfloat16.  Bound: latency, on the path from a partner group's accept mask
+// to this group's: 4.2 us; as rows x units, with the activations
+// through LDS and each output summed over 32 lanes, 7.4 us.
 typedef short da_bf16x4 __attribute__((ext_vector_type(4)));
 typedef float da_f32x16 __attribute__((ext_vector_type(16)));
+typedef float da_f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 da_pair __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ short bf16_bits(float v) {
-    return (short)(__builtin_bit_cast(uint32_t, bf16_round(v)) >> 16);
+// two floats rounded to bfloat16 (to nearest even), in one word
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    const da_f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, da_pair));
 }
 
-template <typename T, int M>
+// The network's matrix instructions in pairs: tiles t and t + 1 of step j (8
+// inputs) of a layer.
+struct DaPair {
+    int layer, t, j;
+};
+constexpr DaPair da_pair_at(int p) {
+    return p < 32   ? DaPair{0, 2 * (p / 16), p % 16}
+           : p < 48 ? DaPair{1, 2 * (p & 1), (p - 32) / 2}
+                    : DaPair{1, 2 * ((p - 48) / 8), 8 + p % 8};
+}
+
+// f(0), f(1), .., f(N - 1) with constant arguments
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_each(F& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+    static_for_each(f, std::make_integer_sequence<int, N>{});
+}
+
+// (before_sums() runs when the matrix instructions are out)
+template <typename T, int M, typename F>
 __device__ __forceinline__ void da_network(SweepShared<T, M, true>& sh, const ChainDesc& cd, int wave, int lane,
-                                           bool da_on, int64_t mv, bool valid, int64_t g) {
+                                           bool da_on, int64_t mv0, int n_movers, int64_t g, F&& before_sums) {
 #ifdef MC_TIMELINE
     // diagnostic build only: stamps of the network phase after the chain stamps
     uint64_t* tln = (uint64_t*)cd.trace_de + kTlSlots * g + 11;
@@ -858,134 +899,127 @@ __device__ __forceinline__ void da_network(SweepShared<T, M, true>& sh, const Ch
     (void)g;
 #endif
     static_assert(M == 4, "the network phase assumes 4 waves");
-    constexpr int WW = 64 / M;        // histogram words logged and cleared per wave
-    constexpr int H1S = 2 * kDaHid + 2;  // row stride in bfloat16 values (odd word stride)
-    static_assert(sizeof(sh.c_own) + sizeof(sh.c_b) >= sizeof(uint16_t) * kGroup * H1S,
-                  "hidden activations must fit in the candidate space");
+    const int half = lane >> 5, row = wave * 32 + (lane & 31), mover = row & 63, pos = row >> 6;
+    const __amdgpu_buffer_rsrc_t wbr = make_rsrc((void*)cd.da_w1b, (uint32_t)(4u * kDaIn * kDaHid));
+    // 4 consecutive inputs k of hidden unit `unit` of layer `layer`
+    auto weights = [&](int layer, int unit, int k) -> da_bf16x4 {
+        if constexpr (SweepShared<T, M, true>::kWtsLds)
+            return *reinterpret_cast<const da_bf16x4*>(&sh.wts[layer * kDaHid + unit][k]);
+        else
+            return __builtin_bit_cast(da_bf16x4, __builtin_amdgcn_raw_buffer_load_b64(
+                                                     wbr, (uint32_t)(2 * ((layer * kDaHid + unit) * kDaIn + k)), 0, 0));
+    };
     __syncthreads();  // every histogram add of this target is done
 #ifdef MC_TIMELINE
     if (stamp) tln[1] = wall_clock64();
 #endif
-    if (valid && mv < cd.log_cap) {
-        uint32_t* dst = cd.log_feat + mv * 64;
+    // this lane's words of its row: counts 8 j + 4 half .. + 3
+    uint32_t words[kDaIn / 8];
 #pragma unroll
-        for (int k = 0; k < WW; ++k) dst[wave * WW + k] = sh.hist[lane][wave * WW + k];
+    for (int j = 0; j < kDaIn / 8; ++j) {
+        uint32_t& w = sh.hist[mover][pos * 32 + 2 * j + half];
+        words[j] = w;
+        w = 0u;
     }
-    uint16_t* h1 = sh.h1();
-    float* outs = &sh.part_out[0][0][0];  // [128] network outputs by row
-    // biases and the last layer are read through a buffer resource: its loads
-    // wait on the vector-memory counter only, so the LDS traffic of this
-    // phase never waits for them (generic-pointer loads count on both)
-    const __amdgpu_buffer_rsrc_t wr = make_rsrc((void*)cd.da_w, (uint32_t)(sizeof(float) * kDaParams));
-    auto wload = [&](int k) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wr, (uint32_t)(4 * k), 0, 0));
-    };
-    constexpr int oB1 = kDaIn * kDaHid, oB2 = oB1 + kDaHid + kDaHid * kDaHid, oW3 = oB2 + kDaHid;
-    // B fragment (4 consecutive inputs k of hidden unit `unit`) of layer `layer`
-    const __amdgpu_buffer_rsrc_t wbr = make_rsrc((void*)cd.da_w1b, (uint32_t)(4u * kDaIn * kDaHid));
-    auto bfrag = [&](int layer, int unit, int k) -> uint2 {
-        if constexpr (SweepShared<T, M, true>::kWtsLds)
-            return *reinterpret_cast<const uint2*>(&sh.wts[layer * kDaHid + unit][k]);
-        else
-            return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(
-                                                 wbr, (uint32_t)(2 * ((layer * kDaHid + unit) * kDaIn + k)), 0, 0));
-    };
-    // this lane's A row
-    const int arow = wave * 32 + (lane & 31);
-    const int amover = arow & 63, apos = arow >> 6;
-    const int kq = (lane >> 5) * 4;
-    // B fragments of a layer: the transposed bfloat16 matrix gives each lane
-    // its four consecutive k of column 32 t + l % 32 in one 8-byte load; all
-    // 64 loads of a layer are issued before its products
-    const int bcol = lane & 31;
+    if (mover < n_movers && mv0 + mover < cd.log_cap) {
+        uint32_t* dst = cd.log_feat + (mv0 + mover) * 64 + pos * 32 + half;
+#pragma unroll
+        for (int j = 0; j < kDaIn / 8; ++j) dst[2 * j] = words[j];
+    }
     if (da_on) {
-        da_f32x16 acc[4];
+        // The 128 matrix instructions go out as 64 pairs, tiles t and t + 1 of
+        // one step of 8 inputs, in an order that leaves the lane work of the
+        // finished tiles (bias, relu, rounding, last layer) to run beside
+        // the next ones; the weights are loaded kAhead pairs ahead.
+        constexpr int kPairs = 64, kAhead = 4;
+        da_bf16x4 wt[kAhead][2];
+        auto fetch = [&](auto pc) __attribute__((always_inline)) {
+            constexpr int p = decltype(pc)::value;
+            constexpr DaPair d = da_pair_at(p);
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                wt[p % kAhead][u] = weights(d.layer, 32 * (d.t + u) + (lane & 31), 8 * d.j + 4 * half);
+        };
+        uint2 x[kDaIn / 8], h[kDaHid / 8];
+        auto convert = [&](int j) {
+            // counts up to 255 are bfloat16 values: the upper halves of the floats
+            uint32_t f[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) f[v] = __builtin_bit_cast(uint32_t, (float)((words[j] >> (8 * v)) & 0xFFu));
+            x[j] = make_uint2(__builtin_amdgcn_perm(f[1], f[0], 0x07060302u),
+                              __builtin_amdgcn_perm(f[3], f[2], 0x07060302u));
+        };
+        da_f32x16 acc1[4], acc2[4];
+        // bf16(relu(acc + bias)) of units 8 j + 4 half .. + 3
+        auto activation = [&](const da_f32x16 (&acc)[4], int which, int j) {
+            const float4 b = *reinterpret_cast<const float4*>(&sh.bias[which][8 * j + 4 * half]);
+            const float bv[4] = {b.x, b.y, b.z, b.w};
+            float r[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float z = acc[j / 4][4 * (j & 3) + v] + bv[v];
+                r[v] = z > 0.f ? z : 0.f;
+            }
+            return make_uint2(bf16_pair(r[0], r[1]), bf16_pair(r[2], r[3]));
+        };
+        // last layer: sum over the units of bf16(relu(Z2 + b2)) w3; unit
+        // 32 t + c, c = 8 q + 4 half + v: over t in order, then over the bits
+        // of c from the lowest
+        float part[4][4];
+        auto last_layer = [&](int j) {
+            const uint2 a = activation(acc2, 1, j);
+            const float4 w = *reinterpret_cast<const float4*>(&sh.bias[2][8 * j + 4 * half]);
+            const float wv[4] = {w.x, w.y, w.z, w.w};
+            const uint32_t hb[4] = {a.x << 16, a.x & 0xFFFF0000u, a.y << 16, a.y & 0xFFFF0000u};
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                part[j & 3][v] = __builtin_fmaf(__builtin_bit_cast(float, hb[v]), wv[v], j < 4 ? 0.f : part[j & 3][v]);
+        };
+        static_for<kAhead>(fetch);
+        convert(0);
+        convert(1);
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-#pragma unroll 2
-        for (int j = 0; j < kDaIn / 8; ++j) {
-            const uint32_t w = sh.hist[amover][apos * 32 + (8 * j + kq) / 4];
-            da_bf16x4 a;
+            for (int r = 0; r < 16; ++r) acc1[t][r] = acc2[t][r] = 0.f;
+        static_for<kPairs>([&](auto pc) __attribute__((always_inline)) {
+            constexpr int p = decltype(pc)::value;
+            constexpr DaPair d = da_pair_at(p);
+            const da_bf16x4 in = __builtin_bit_cast(da_bf16x4, d.layer ? h[d.j] : x[d.j]);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) a[v] = bf16_bits((float)((w >> (8 * v)) & 0xFFu));
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const uint2 bv = bfrag(0, 32 * t + bcol, 8 * j + kq);
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, __builtin_bit_cast(da_bf16x4, bv), acc[t], 0, 0, 0);
+            for (int u = 0; u < 2; ++u) {
+                da_f32x16& c = d.layer ? acc2[d.t + u] : acc1[d.t + u];
+                c = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(wt[p % kAhead][u], in, c, 0, 0, 0);
             }
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int col = 32 * t + (lane & 31);
-            const float bias = wload(oB1 + col);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int r = wave * 32 + 8 * (i / 4) + 4 * (lane >> 5) + (i % 4);
-                const float z = acc[t][i] + bias;
-                h1[(r & 63) * H1S + (r >> 6) * kDaHid + col] = (uint16_t)bf16_bits(z > 0.f ? z : 0.f);
-            }
-        }
-    }
-    __syncthreads();  // first hidden layer complete
+            if constexpr (p + kAhead < kPairs) fetch(std::integral_constant<int, p + kAhead>{});
+            if constexpr (p + 2 < 16) convert(p + 2);
+            if constexpr (p >= 16 && p < 48 && (p & 1)) h[(p - 16) / 2] = activation(acc1, 0, (p - 16) / 2);
+            if constexpr (p > 56) last_layer(p - 57);
+            __builtin_amdgcn_sched_barrier(0);
 #ifdef MC_TIMELINE
-    if (stamp) tln[2] = wall_clock64();
+            if (p == 31 && stamp) tln[2] = wall_clock64();
 #endif
+        });
+        before_sums();
 #pragma unroll
-    for (int k = 0; k < WW; ++k) sh.hist[lane][wave * WW + k] = 0u;
-    if (da_on) {
-        da_f32x16 acc[4];
+        for (int j = 7; j < 16; ++j) last_layer(j);
+        float sum[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-        const uint16_t* arow_h = h1 + amover * H1S + apos * kDaHid;
-#pragma unroll 2
-        for (int j = 0; j < kDaHid / 8; ++j) {
-            const uint32_t lo = *reinterpret_cast<const uint32_t*>(arow_h + 8 * j + kq);
-            const uint32_t hi = *reinterpret_cast<const uint32_t*>(arow_h + 8 * j + kq + 2);
-            uint2 av;
-            av.x = lo;
-            av.y = hi;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const uint2 bv = bfrag(1, 32 * t + bcol, 8 * j + kq);
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(da_bf16x4, av),
-                                                                  __builtin_bit_cast(da_bf16x4, bv), acc[t], 0, 0, 0);
-            }
+        for (int q = 0; q < 4; ++q) {
+            sum[q] = (part[q][0] + part[q][1]) + (part[q][2] + part[q][3]);
+            sum[q] += __shfl_xor(sum[q], 32, 64);
         }
-        // last layer: sum over the columns of bf16(relu(Z2 + b2)) w3
-        float part[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) part[i] = 0.f;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int col = 32 * t + (lane & 31);
-            const float bias = wload(oB2 + col), wc = wload(oW3 + col);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float z = acc[t][i] + bias;
-                part[i] = __builtin_fmaf(bf16_round(z > 0.f ? z : 0.f), wc, part[i]);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-#pragma unroll
-            for (int d = 1; d < 32; d <<= 1) part[i] += __shfl_xor(part[i], d, 64);
-        }
-        if ((lane & 31) == 0) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) outs[wave * 32 + 8 * (i / 4) + 4 * (lane >> 5) + (i % 4)] = part[i];
-        }
+        sh.net_out[row] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    } else {
+        before_sums();
     }
-    __syncthreads();  // outputs complete; the candidate space is free again
+    __syncthreads();  // outputs complete, histograms clear
 #ifdef MC_TIMELINE
     if (stamp) tln[3] = wall_clock64();
 #endif
     if (da_on && wave == 0) {
-        const float b3 = wload(kDaParams - 1);
-        const float o0 = b3 + outs[lane], o1 = b3 + outs[64 + lane];
+        const float b3 = sh.bias3;
+        const float o0 = b3 + sh.net_out[lane], o1 = b3 + sh.net_out[64 + lane];
         sh.deh[lane] = cd.lB * ((double)o1 - (double)o0);
     }
 }
@@ -1033,6 +1067,16 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
     // the delayed-acceptance switch is constant during a launch (the drift
     // monitor changes it between launches)
     const bool da_on = DA && cd.da != nullptr && cd.da->active != 0 && cd.da_w != nullptr;
+    const float inv_dr = DA ? (float)(1.0 / cd.da_dr) : 0.f;
+    if constexpr (DA) {
+        if (da_on) {
+            if (threadIdx.x == 0) sh.bias3 = cd.da_w[kDaParams - 1];
+            for (int k = threadIdx.x; k < 3 * kDaHid; k += 64 * M) {
+                const int u = k % kDaHid, o_b2 = kDaIn * kDaHid + kDaHid + kDaHid * kDaHid;
+                sh.bias[k / kDaHid][u] = cd.da_w[(k < kDaHid ? kDaIn * kDaHid : k < 2 * kDaHid ? o_b2 : o_b2 + kDaHid) + u];
+            }
+        }
+    }
     if constexpr (SweepShared<T, M, DA>::kWtsLds) {
         if (da_on) {
             static_assert(kDaIn == kDaHid, "both matrices are 128 x 128");
@@ -1063,6 +1107,12 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
             const T hi = UNIFORM_SIGMA ? hu : half[ion];
             MoverInputs mi{};
             if (wave == 0) mi = mover_inputs(cd, ion, qi, txi, tyi, tzi, wd.w);
+            if constexpr (DA) {
+                if (wave == 0 && da_on) {  // here, not in the chain step that the next groups wait for
+                    mi.log_u2 = log(accept_uniform(move_words(cd.seed, cd.chain_id, (uint32_t)s, (uint32_t)ion, 2u).x));
+                    asm volatile("" : "+v"(mi.log_u2));
+                }
+            }
 
 #ifdef MC_TIMELINE
             if (!DA && wave == 0 && lane == 0 && kTlSlots * (g + 1) <= cd.trace_cap)
@@ -1078,8 +1128,8 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
             {
                 if (lane >= wave * P && lane < wave * P + P) {
                     const int m = lane - wave * P;
-                    sh.st_old[wave][m] = mk4<T>(xi, yi, zi, qi);
-                    sh.st_new[wave][m] = mk4<T>(txi, tyi, tzi, qi);
+                    sh.old_of(wave)[m] = mk4<T>(xi, yi, zi, qi);
+                    sh.new_of(wave)[m] = mk4<T>(txi, tyi, tzi, qi);
                     sh.st_half[wave][m] = hi;
                 }
                 wave_lds_sync();
@@ -1087,8 +1137,8 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
 #pragma unroll
                 for (int m = 0; m < P; ++m) {
                     const int j = wave * P + m;
-                    const T4 po = sh.st_old[wave][m];
-                    const T4 pt = sh.st_new[wave][m];
+                    const T4 po = sh.old_of(wave)[m];
+                    const T4 pt = sh.new_of(wave)[m];
                     const T hj = UNIFORM_SIGMA ? hu : sh.st_half[wave][m];
                     const T s_ij = hi + hj;
                     const T d2o = Prec<T>::norm2(po.x - xi, po.y - yi, po.z - zi);
@@ -1114,8 +1164,8 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                         if (j > lane) {  // not moved yet: its current position counts
                             const double qq = (double)po.w * (double)qi;
                             if (qq != 0.0) {
-                                da_hist_add(sh, cd, lane, 0, qq < 0.0, d2_exact(xi, yi, zi, po.x, po.y, po.z));
-                                da_hist_add(sh, cd, lane, 1, qq < 0.0, d2_exact(txi, tyi, tzi, po.x, po.y, po.z));
+                                da_hist_add(sh, cd, inv_dr, lane, 0, qq < 0.0, d2_exact(xi, yi, zi, po.x, po.y, po.z));
+                                da_hist_add(sh, cd, inv_dr, lane, 1, qq < 0.0, d2_exact(txi, tyi, tzi, po.x, po.y, po.z));
                             }
                         } else if (j < lane) {  // decision pending: conflict rule
                             const double rc2 = cd.da_rc * cd.da_rc;
@@ -1150,8 +1200,8 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                     if (lane < P) {
                         const T qj = charge[j];
                         const uint4 wj = move_words(cd.seed, cd.chain_id, (uint32_t)sp, (uint32_t)j);
-                        sh.st_old[wave][lane] = mk4<T>(pr.x, pr.y, pr.z, qj);
-                        sh.st_new[wave][lane] = mk4<T>(trial_coord((T)pr.x, wj.x, D), trial_coord((T)pr.y, wj.y, D),
+                        sh.old_of(wave)[lane] = mk4<T>(pr.x, pr.y, pr.z, qj);
+                        sh.new_of(wave)[lane] = mk4<T>(trial_coord((T)pr.x, wj.x, D), trial_coord((T)pr.y, wj.y, D),
                                                         trial_coord((T)pr.z, wj.z, D), qj);
                         if (!UNIFORM_SIGMA) sh.st_half[wave][lane] = half[j];
                     }
@@ -1159,8 +1209,8 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                     T sf = 0;
 #pragma unroll
                     for (int m = 0; m < P; ++m) {
-                        const T4 po = sh.st_old[wave][m];
-                        const T4 pt = sh.st_new[wave][m];
+                        const T4 po = sh.old_of(wave)[m];
+                        const T4 pt = sh.new_of(wave)[m];
                         const T hj = UNIFORM_SIGMA ? hu : sh.st_half[wave][m];
                         const T s_ij = hi + hj;
                         const T d2o = Prec<T>::norm2(po.x - xi, po.y - yi, po.z - zi);
@@ -1185,8 +1235,8 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                                 // ion sits at its starting position, which counts
                                 const double qq = (double)po.w * (double)qi;
                                 if (qq != 0.0) {
-                                    da_hist_add(sh, cd, lane, 0, qq < 0.0, d2_exact(xi, yi, zi, po.x, po.y, po.z));
-                                    da_hist_add(sh, cd, lane, 1, qq < 0.0, d2_exact(txi, tyi, tzi, po.x, po.y, po.z));
+                                    da_hist_add(sh, cd, inv_dr, lane, 0, qq < 0.0, d2_exact(xi, yi, zi, po.x, po.y, po.z));
+                                    da_hist_add(sh, cd, inv_dr, lane, 1, qq < 0.0, d2_exact(txi, tyi, tzi, po.x, po.y, po.z));
                                 }
                             }
                         }
@@ -1228,14 +1278,10 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                         sh.c_b[kb][lane][wave * P + m] = c_band[kb][m];  // zero beyond the band
                 }
             };
-            if constexpr (!DA) {
-                // complete from here on: handed off now, off the critical
-                // path, once the chain wave has released the previous target
-                // (the delayed-acceptance kernels reuse this LDS for the
-                // network and hand off at the end)
-                wait_lds_at_least(&sh.consumed, t, ctl);
-                hand_off_candidates();
-            }
+            // complete from here on: handed off now, off the critical path,
+            // once the chain wave has released the previous target
+            wait_lds_at_least(&sh.consumed, t, ctl);
+            hand_off_candidates();
 
             // ---- decided partner groups g-nb+1 .. g-band-1, in stream order.  The next
             // tile is loaded speculatively while this one is computed (float path); a
@@ -1263,10 +1309,119 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                 // uniform diameters: overlap with any of these partners iff the
                 // smallest trial distance is below the contact distance
                 T d2t_min = (T)3.0e38;
+                // Delayed acceptance: the partners within range of a mover are
+                // few (one in a thousand pairs at the usual range), so they
+                // are only noted in the pair loop, as a ballot per partner,
+                // and go to the wave's ring; the exact distances and bins (a
+                // double sqrt and division each) are worked out for 64 of
+                // them at a time, a lane each.  Bound: the pair terms.
+                // Binning each tile's few at once, one or two lanes at work,
+                // cost every tile that had any the whole chain of double
+                // operations.
+                uint32_t q_in = 0, q_out = 0;
+                auto bin_near = [&](uint32_t count) {
+                    wave_lds_sync();
+                    const uint32_t k = (uint32_t)lane < count ? (uint32_t)lane : count - 1u;
+                    const T4 e = sh.near[wave][(q_out + k) & (kNearRing - 1)];
+                    const int code = (int)e.w;
+                    const int l = code & 63;
+                    const T ox = __shfl(xi, l, 64), oy = __shfl(yi, l, 64), oz = __shfl(zi, l, 64);
+                    const T nx = __shfl(txi, l, 64), ny = __shfl(tyi, l, 64), nz = __shfl(tzi, l, 64);
+                    if ((uint32_t)lane < count) {
+                        da_hist_add(sh, cd, inv_dr, l, 0, code >= 64, d2_exact(ox, oy, oz, e.x, e.y, e.z));
+                        da_hist_add(sh, cd, inv_dr, l, 1, code >= 64, d2_exact(nx, ny, nz, e.x, e.y, e.z));
+                    }
+                    q_out += count;
+                    wave_lds_sync();
+                };
+                // to the ring: the movers near_of[m] near partner st[m]
+                auto note_near = [&](const T4* st, const uint64_t (&near_of)[DA ? P : 1], uint64_t near_any) {
+                    if (near_any != 0ull) {
+#pragma unroll
+                        for (int m = 0; m < P; ++m) {
+                            if (near_of[m] != 0ull) {
+                                const T4 p = st[m];
+                                const double qq = (double)p.w * (double)qi;
+                                const bool put = ((near_of[m] >> lane) & 1ull) != 0 && qq != 0.0;
+                                const uint64_t who = __ballot(put);
+                                if (put)
+                                    sh.near[wave][(q_in + __builtin_amdgcn_mbcnt_hi(
+                                                              (uint32_t)(who >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u))) &
+                                                  (kNearRing - 1)] =
+                                        mk4<T>(p.x, p.y, p.z, (T)(lane + (qq < 0.0 ? 64 : 0)));
+                                q_in += (uint32_t)__popcll(who);
+                                if (q_in - q_out >= 64u) bin_near(64u);
+                            }
+                        }
+                    }
+                };
                 // a working-precision squared distance below this bound may be
                 // below rc^2 exactly (the bound is a relative 1e-5 above it)
                 const T rc2_wide = (T)(cd.da_rc * cd.da_rc * (1.0 + 1e-5));
-                for (int64_t gp = g - nb + 1 + dphase; gp <= g_last; gp += KD) {
+                // the terms of one staged slice of P partners of one diameter
+                auto slice_sum = [&](const T4* st) {
+                    T sf = 0;
+                    uint64_t near_of[DA ? P : 1], near_any = 0;  // delayed acceptance: movers possibly within rc
+#pragma unroll
+                    for (int m = 0; m < P; ++m) {
+                        const T4 p = st[m];
+                        const T d2 = Prec<T>::norm2(p.x - xi, p.y - yi, p.z - zi);
+                        const T d2t = Prec<T>::norm2(p.x - txi, p.y - tyi, p.z - tzi);
+                        sf = Prec<T>::fma(p.w, Prec<T>::rinv(d2t) - Prec<T>::rinv(d2), sf);
+                        d2t_min = Prec<T>::min(d2t, d2t_min);
+                        near_of[m] = __ballot(Prec<T>::min(d2, d2t) < rc2_wide);
+                        near_any |= near_of[m];
+                    }
+                    note_near(st, near_of, near_any);
+                    S += (double)sf;
+                };
+                int64_t gp = g - nb + 1 + dphase;
+                // Delayed acceptance, float, uniform diameters: while the
+                // groups are well before the target, a wave takes its slices
+                // of four of them at once, a record a lane (16 of 64 lanes
+                // load for one slice), loaded four slices ahead.  The slices'
+                // sums stay as they are.  Not for the last kQuadMargin groups,
+                // which the chain is still deciding.  Bound: the pair terms;
+                // one slice at a time, with one workgroup a CU, every slice
+                // waited for its records (ten sweeps of N = 32768 14.6 ms,
+                // 13.0 so).  The plain kernels have a second workgroup to fill
+                // that wait: no gain at N = 32768, 3 % lost at 4001.
+                if constexpr (DA && UNIFORM_SIGMA && SweepShared<T, M, DA>::SW == kGroup) {
+                    const int64_t q_last = g_last - kQuadMargin;
+                    const int sub = lane / P, jq = wave * P + lane % P;
+                    typename IO::Rec rec{};
+                    T qc = 0;
+                    uint32_t slot = 0, ver = 0;
+                    auto next = [&]() {
+                        int bl = bp + sub;
+                        ver = (uint32_t)sp;
+                        if (bl >= nb) {
+                            bl -= nb;
+                            ++ver;
+                        }
+                        const int j = bl * kGroup + jq;
+                        slot = (ver & 1u) * (uint32_t)npad + (uint32_t)j;
+                        rec = IO::load(pos_r, slot);
+                        qc = charge[j];
+                    };
+                    if (gp + 3 <= q_last) next();
+                    for (; gp + 3 <= q_last; gp += 4) {
+                        if (__ballot(rec.ver != ver) != 0ull) rec = IO::load_valid(pos_r, slot, ver, true, ctl, true);
+                        sh.st[wave][lane] = mk4<T>(rec.x, rec.y, rec.z, qc);
+                        wave_lds_sync();
+                        bp += 4;
+                        if (bp >= nb) {
+                            bp -= nb;
+                            ++sp;
+                        }
+                        if (gp + 7 <= q_last) next();
+#pragma nounroll
+                        for (int u = 0; u < 4; ++u) slice_sum(sh.st[wave] + u * P);
+                        wave_lds_sync();
+                    }
+                }
+                for (; gp <= g_last; gp += KD) {
                     const int j = bp * kGroup + jl;
                     typename IO::Rec cur;
                     if (have_next && __ballot(lane < PD && nxt.ver != (uint32_t)sp) == 0ull)
@@ -1286,7 +1441,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                     if (lane < PD) {
                         const bool lo = PD == P || lane < P;
                         const int ls = lo ? lane : lane - P;
-                        (lo ? sh.st_old[wave] : sh.st_old2[wave])[ls] = mk4<T>(cur.x, cur.y, cur.z, charge[j]);
+                        (lo ? sh.old_of(wave) : sh.st_old2[wave])[ls] = mk4<T>(cur.x, cur.y, cur.z, charge[j]);
                         if (!UNIFORM_SIGMA) {
                             hj0 = half[j];
                             (lo ? sh.st_half[wave] : sh.st_half2[wave])[ls] = hj0;
@@ -1313,7 +1468,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                         }
                     }
                     T sf = 0;
-                    uint32_t nearm = 0;  // delayed acceptance: partners possibly within rc
+                    uint64_t near_of[DA ? P : 1], near_any = 0;  // delayed acceptance: movers possibly within rc
                     if constexpr (UNIFORM_SIGMA || DA) {
                         // P partners at a time (a loop, not unrolled, so that a
                         // round needs the registers of one P-partner slice)
@@ -1322,7 +1477,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
 #pragma unroll
                         for (int mm = 0; mm < P; ++mm) {
                             const int m = c * P + mm;
-                            const T4 p = c == 0 ? sh.st_old[wave][mm] : sh.st_old2[wave][(c - 1) * P + mm];
+                            const T4 p = c == 0 ? sh.old_of(wave)[mm] : sh.st_old2[wave][(c - 1) * P + mm];
                             const T hj = UNIFORM_SIGMA ? hu
                                          : c == 0 ? sh.st_half[wave][mm] : sh.st_half2[wave][(c - 1) * P + mm];
                             const T s_ij = hi + hj;
@@ -1333,7 +1488,10 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                                 d2t_min = Prec<T>::min(d2t, d2t_min);
                             else
                                 ov |= d2t < s_ij * s_ij;
-                            if constexpr (DA) nearm |= (uint32_t)(Prec<T>::min(d2, d2t) < rc2_wide) << m;
+                            if constexpr (DA) {
+                                near_of[m] = __ballot(Prec<T>::min(d2, d2t) < rc2_wide);
+                                near_any |= near_of[m];
+                            }
                         }
                     } else {
                         // per-ion diameters: the contact test per pair, or as a
@@ -1348,7 +1506,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                             for (int c = 0; c < KD; ++c)
 #pragma unroll
                             for (int mm = 0; mm < P; ++mm) {
-                                const T4 p = c == 0 ? sh.st_old[wave][mm] : sh.st_old2[wave][(c - 1) * P + mm];
+                                const T4 p = c == 0 ? sh.old_of(wave)[mm] : sh.st_old2[wave][(c - 1) * P + mm];
                                 const T d2 = Prec<T>::norm2(p.x - xi, p.y - yi, p.z - zi);
                                 const T d2t = Prec<T>::norm2(p.x - txi, p.y - tyi, p.z - tzi);
                                 sf = Prec<T>::fma(p.w, Prec<T>::rinv(d2t) - Prec<T>::rinv(d2), sf);
@@ -1371,22 +1529,14 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                             slice_terms(std::true_type{});
                     }
                     if constexpr (DA) {
-                        // rare: bin the near partners with exact double distances
-                        if (__ballot(nearm != 0u) != 0ull) {
-                            while (nearm) {
-                                const int m = __builtin_ctz(nearm);
-                                nearm &= nearm - 1u;
-                                const T4 p = sh.st_old[wave][m];
-                                const double qq = (double)p.w * (double)qi;
-                                if (qq != 0.0) {
-                                    da_hist_add(sh, cd, lane, 0, qq < 0.0, d2_exact(xi, yi, zi, p.x, p.y, p.z));
-                                    da_hist_add(sh, cd, lane, 1, qq < 0.0, d2_exact(txi, tyi, tzi, p.x, p.y, p.z));
-                                }
-                            }
-                        }
+                        note_near(sh.old_of(wave), near_of, near_any);
                     }
                     S += (double)sf;
                     wave_lds_sync();
+                    if constexpr (DA) {
+                        // the ring is empty but for the last tile's when that comes
+                        if (gp + 2 * KD > g_last && q_in != q_out) bin_near(q_in - q_out);
+                    }
                     bp = bn;
                     sp = sn;
                 }
@@ -1397,23 +1547,26 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                 ((uint64_t*)cd.trace_de)[kTlSlots * g + 12] = wall_clock64();
 #endif
 
+            GroupRec rb[KB];
+            auto load_band_recs = [&]() {  // all loads in flight at once
+#pragma unroll
+                for (int kb = LC; kb < KB; ++kb)
+                    if (kb < band) rb[kb] = load_rec(rec_r, (uint32_t)((g - 1 - kb) & (kRing - 1)));
+            };
             // ---- delayed acceptance: the features are complete after the
             // last partner tile, so the network runs here, while the older
             // band groups' accept masks are still on their way
             if constexpr (DA) {
-                wait_lds_at_least(&sh.consumed, t, ctl);
                 const uint64_t cb = __ballot(conf);
                 if (lane == 0) sh.part_conf[wave] = cb;
-                da_network<T, M>(sh, cd, wave, lane, da_on, s * (int64_t)cd.n + ion, ion < cd.n, g);
+                da_network<T, M>(sh, cd, wave, lane, da_on, s * (int64_t)cd.n + b * kGroup, cd.n - b * kGroup, g,
+                                 load_band_recs);
             }
 
+            if constexpr (!DA) load_band_recs();
             // ---- band groups older than the chain step's: their accept
             // masks are out by now (published about one group after the last
             // partner tile); this wave's slice of their candidates becomes final
-            GroupRec rb[KB];
-#pragma unroll
-            for (int kb = LC; kb < KB; ++kb)  // all loads in flight at once
-                if (kb < band) rb[kb] = load_rec(rec_r, (uint32_t)((g - 1 - kb) & (kRing - 1)));
 #pragma unroll
             for (int kb = KB - 1; kb >= LC; --kb) {
                 if (kb < band) {
@@ -1436,8 +1589,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
             if (!DA && lane == 0 && kTlSlots * (g + 1) <= cd.trace_cap)
                 ((uint64_t*)cd.trace_de)[kTlSlots * g + (wave == 0 ? 13 : 20 + wave)] = wall_clock64();
 #endif
-            // ---- hand off to the chain wave once it has released the previous target
-            if constexpr (DA) hand_off_candidates();
+            // ---- hand off the sums to the chain wave
             sh.part_s[wave][lane] = S;
             {
                 const uint64_t ob = __ballot(ov);
