@@ -15,7 +15,7 @@ BLOCKS = [("W1", 0, 128 * 128), ("b1", 128 * 128, 128), ("W2", 128 * 128 + 128, 
           ("b2", 2 * 128 * 128 + 128, 128), ("w3", 2 * 128 * 128 + 256, 128)]
 
 
-@pytest.mark.parametrize("batch", [32, 96, 128, 160, 288])
+@pytest.mark.parametrize("batch", [32, 96, 128, 160, 288, 1024, 1056])
 def test_gradients_at_tile_remainders(oracle, batch):
     from paper_1602_05716_amd import mc
     rng = np.random.default_rng(1000 + batch)
