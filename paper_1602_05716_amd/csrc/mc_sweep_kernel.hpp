@@ -1453,13 +1453,14 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                         slice_uniform = __ballot(lane < PD && hjl != hj0) == 0ull;
                     }
                     wave_lds_sync();
-                    int bn = bp;
+                    // (KD steps of one, compared one by one, were 1.2 % of a sweep
+                    // of N = 131072: 7.95 ms, 7.86 so)
+                    int bn = bp + KD;
                     int64_t sn = sp;
-                    for (int k = 0; k < KD; ++k)
-                        if (++bn == nb) {
-                            bn = 0;
-                            ++sn;
-                        }
+                    while (bn >= nb) {
+                        bn -= nb;
+                        ++sn;
+                    }
                     have_next = false;
                     if constexpr (sizeof(T) == 4) {
                         if (gp + KD <= g_last) {
