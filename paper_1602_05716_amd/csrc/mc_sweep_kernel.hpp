@@ -304,9 +304,9 @@ struct SweepShared {
     // corrections, one padded row per mover i (16-byte reads of 4 partners
     // are free of bank conflicts)
     static constexpr int CS = kGroup + (sizeof(T) == 4 ? 4 : 2);
-    T c_own[kGroup][CS];           // own group [mover i][partner j]
-    T c_b[LC][kGroup][CS];         // group g-1-kb [mover i][partner j]
-    T fac[kGroup];                 // chain wave: 0/1 factors of a row sum's mask
+    alignas(16) T c_own[kGroup][CS];    // own group [mover i][partner j]
+    alignas(16) T c_b[LC][kGroup][CS];  // group g-1-kb [mover i][partner j]
+    alignas(16) T fac[kGroup];          // chain wave: 0/1 factors of a row sum's mask
     int ready;                  // compute waves done filling the hand-off for the current target
     int consumed;               // local target index + 1 the chain wave last released
     // the helper wave's part of the chain step: band corrections of groups
@@ -314,7 +314,7 @@ struct SweepShared {
     // and the local target index + 1 it last finished
     double h_corr[LC > 1 ? kGroup : 1];
     uint64_t h_ov;
-    T fac_h[LC > 1 ? kGroup : 1];
+    alignas(LC > 1 ? 16 : alignof(T)) T fac_h[LC > 1 ? kGroup : 1];
     int h_done;
     // delayed acceptance: per mover, byte histograms of neighbour distances at
     // the old position (bytes 0..127) and at the trial position (128..255),
@@ -330,8 +330,9 @@ struct SweepShared {
     // bfloat16, rows padded to 132 values (8-byte reads free of bank
     // conflicts); loaded once per launch
     static constexpr bool kWtsLds = DA && sizeof(T) == 4;  // (the double kernel reads them from memory)
-    uint16_t wts[kWtsLds ? 2 * kDaHid : 1][kWtsLds ? kDaIn + 4 : 1];
-    // placed last, so that the fields above keep their offsets
+    alignas(16) uint16_t wts[kWtsLds ? 2 * kDaHid : 1][kWtsLds ? kDaIn + 4 : 1];
+    static_assert(!kWtsLds || sizeof(wts[0]) % 8 == 0, "rows of 8-byte pieces");
+    // a decided tile's partners beyond the first P
     T4 st_old2[M][PD > P ? PD - P : 1];
     T st_half2[M][PD > P ? PD - P : 1];
     // delayed acceptance: per wave, a ring of partners found near a mover

@@ -58,6 +58,7 @@ __device__ __forceinline__ float from_bf16(uint16_t h) { return __builtin_bit_ca
 // then spread over the banks).
 constexpr int kRowPad = kHid + 4;
 typedef uint16_t row_t[kRowPad];
+static_assert(sizeof(row_t) % 8 == 0, "rows of 8-byte pieces");
 
 // acc[t] += A[32 x 128] B[128 x 32] for two neighbouring column tiles: rows
 // row0.. of `a` ([row][k]) and rows col0.., col0 + 32.. of `b` ([column][k]),
@@ -102,9 +103,9 @@ struct StepBuffers {
 };
 
 struct RowsShared {
-    row_t x[64];      // input rows, then H2, then dZ2
-    row_t h[64];      // H1, then dZ1
-    row_t w1t[kHid], w2t[kHid], w2[kHid];
+    alignas(16) row_t x[64];  // input rows, then H2, then dZ2
+    alignas(16) row_t h[64];  // H1, then dZ1
+    alignas(16) row_t w1t[kHid], w2t[kHid], w2[kHid];
     float b1[kHid], b2[kHid], w3[kHid];
     float dout[64];
 };
