@@ -1154,7 +1154,7 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
                 (rc = dalloc(h, &c.log_deh, sizeof(double) * c.log_cap)) ||
                 (rc = dalloc(h, &c.log_flags, (size_t)c.log_cap)))
                 return bail(rc);
-            if (hipMemset(c.log_flags, 0, (size_t)c.log_cap) != hipSuccess) {
+            if (hipMemsetAsync(c.log_flags, 0, (size_t)c.log_cap, h->stream) != hipSuccess) {
                 h->err = "clearing the log failed";
                 return bail(MC_E_DEVICE);
             }

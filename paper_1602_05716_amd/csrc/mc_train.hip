@@ -487,11 +487,13 @@ struct Net {
         (void)hipFree(own);
     }
     // P from host memory (and, of a gradient pass, the staged inputs behind
-    // it: `bytes` in all), and the working copies
+    // it: `bytes` in all), and the working copies.  The moments are cleared on
+    // the stream that uses them: a handle's stream does not wait for the null
+    // stream, and a clear need not be done when its call returns
     bool upload_params(const void* p, size_t bytes = 4 * kNP) {
         if (hipMemcpy(P, p, bytes, hipMemcpyHostToDevice) != hipSuccess) return false;
-        if (m && hipMemset(m, 0, 4 * kNP) != hipSuccess) return false;
-        if (v && hipMemset(v, 0, 4 * kNP) != hipSuccess) return false;
+        if (m && hipMemsetAsync(m, 0, 4 * kNP, s) != hipSuccess) return false;
+        if (v && hipMemsetAsync(v, 0, 4 * kNP, s) != hipSuccess) return false;
         hipLaunchKernelGGL(refresh_kernel, dim3((kNP + 255) / 256), dim3(256), 0, s, P, kNP, Pw, W1t, W2t, W2b);
         return hipGetLastError() == hipSuccess;
     }
