@@ -2115,11 +2115,19 @@ int mc_set_surrogate(mc_handle* h, int32_t chain, const double* params, double r
     }
     int rc = sync_check(h);
     if (rc) return rc;
+    // what can be refused is refused before a chain is changed
+    if (!h->da_kernel && (int)h->chains.size() > h->cap_da)
+        return fail(h, MC_E_ARG, "more chains than co-resident workgroups of the delayed-acceptance kernel");
+    const auto given = [&](int32_t k) { return chain < 0 || k == chain; };
     for (int32_t k = 0; k < (int32_t)h->chains.size(); ++k) {
-        if (chain >= 0 && k != chain) continue;
         Chain& c = h->chains[k];
-        if (!c.da_w && (rc = dalloc(h, &c.da_w, sizeof(float) * kDaParams))) return rc;
-        if (!c.da_wb && (rc = dalloc(h, &c.da_wb, sizeof(uint16_t) * wb.size()))) return rc;
+        if (given(k) && ((!c.da_w && (rc = dalloc(h, &c.da_w, sizeof(float) * kDaParams))) ||
+                         (!c.da_wb && (rc = dalloc(h, &c.da_wb, sizeof(uint16_t) * wb.size())))))
+            return rc;
+    }
+    for (int32_t k = 0; k < (int32_t)h->chains.size(); ++k) {
+        if (!given(k)) continue;
+        Chain& c = h->chains[k];
         HIPCHECK(h, hipMemcpy(c.da_w, w.data(), sizeof(float) * kDaParams, hipMemcpyHostToDevice));
         HIPCHECK(h, hipMemcpy(c.da_wb, wb.data(), sizeof(uint16_t) * wb.size(), hipMemcpyHostToDevice));
         unsigned long long st[ST_N];
@@ -2142,8 +2150,6 @@ int mc_set_surrogate(mc_handle* h, int32_t chain, const double* params, double r
     }
     h->da_window = h->opt.da_window;
     if (!h->da_kernel) {
-        if ((int)h->chains.size() > h->cap_da)
-            return fail(h, MC_E_ARG, "more chains than co-resident workgroups of the delayed-acceptance kernel");
         h->da_kernel = true;
         h->waves = 4;  // (a double handle's automatic eight end here)
         // the kernel serves every chain of the handle, surrogate or not
