@@ -423,8 +423,13 @@ rdf_scatter_kernel(const ChainDesc* __restrict__ chains, const BlockItem* __rest
 // sorted order.  The block's eight waves share the partners, 64 at a time.
 // A persistent grid: each block takes items in turn and adds its LDS
 // histogram to the chain's once per chain (3200 bins by hundreds of blocks
-// are as many atomics as a sample has pairs to bin).
+// are as many atomics as a sample has pairs to bin), or sooner where a
+// counter could wrap.
 constexpr int kRdfWaves = 8;
+// The histogram's counters have 32 bits and an item adds at most 64 n to one,
+// so it is also added (and cleared) after this many items of a chain: 3 at
+// n = 2^24; up to n = 1.4e6 a block of 512 has fewer items in all.
+__host__ __device__ constexpr int rdf_items_per_flush(int n) { return (int)(0xFFFFFFFFull / (64ull * (unsigned)n)); }
 template <typename T>
 __global__ void __launch_bounds__(64 * kRdfWaves)
 rdf_count_kernel(const ChainDesc* __restrict__ chains, const BlockItem* __restrict__ items, int n_items, double rmax,
@@ -436,7 +441,7 @@ rdf_count_kernel(const ChainDesc* __restrict__ chains, const BlockItem* __restri
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const double rmax2 = rmax * rmax * (1.0 + 1e-12);
     const float inv_dr = (float)(1.0 / dr), near = 1e-4f + 1e-6f * (float)bins;
-    int chain = -1, nh = 0;
+    int chain = -1, nh = 0, room = 0;  // room: items before the next flush
     auto flush = [&]() {
         __syncthreads();
         if (chain >= 0)
@@ -446,13 +451,15 @@ rdf_count_kernel(const ChainDesc* __restrict__ chains, const BlockItem* __restri
     };
     for (int q = blockIdx.x; q < n_items; q += gridDim.x) {
         const BlockItem item = items[q];
-        if (item.chain != chain) {
+        if (item.chain != chain || room == 0) {
             flush();
             chain = item.chain;
             nh = chains[chain].ntypes * chains[chain].ntypes * bins;
+            room = rdf_items_per_flush(chains[chain].n);
             for (int k = threadIdx.x; k < nh; k += blockDim.x) hist[k] = 0u;
             __syncthreads();
         }
+        --room;
         const ChainDesc& cd = chains[chain];
         const T4* __restrict__ ions = (const T4*)cd.rdf_sorted;
         const int n = cd.n, side = cd.rdf_side, ntypes = cd.ntypes;
