@@ -77,16 +77,17 @@ struct BlockItem {
     int32_t part;
 };
 
-// Blocks per pair of super-rows of the re-sum (below) for a chain of nb
-// groups in a handle whose chains have total_pairs such pairs: enough blocks
-// for eight a CU (2048 in all), while every wave keeps at least two tiles.
-__host__ __device__ inline int energy_split(int nb, int total_pairs) {
-    const int want = (2048 + total_pairs - 1) / total_pairs;
+// Pairs of super-rows of a chain of nb groups, for the re-sum (below).
+__host__ __device__ inline int energy_pairs(int nb) { return ((nb + 1) / 2 + 1) / 2; }
+// Blocks per pair of super-rows: enough for eight a CU (2048 in all) from the
+// chain alone, while every wave keeps at least two tiles.  From the chain
+// only, so that the order of its sum, and with it the last bits of its
+// energy, is the same whatever other chains its handle holds.
+__host__ __device__ inline int energy_split(int nb) {
+    const int want = (2048 + energy_pairs(nb) - 1) / energy_pairs(nb);
     const int most = nb / 8;
     return want < most ? want : (most > 1 ? most : 1);
 }
-// Pairs of super-rows of a chain of nb groups.
-__host__ __device__ inline int energy_pairs(int nb) { return ((nb + 1) / 2 + 1) / 2; }
 
 // Positions are read as {x, y, z, *} records (the fourth word is the sweep
 // version tag of the sweep kernel) from the image of the given parity, and

@@ -985,15 +985,12 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
     plan.add(&h->d_desc, sizeof(ChainDesc) * n_chains);
     plan.add(&h->d_wgmap, sizeof(int2) * (h->cap + n_chains));
     plan.add(&h->d_wgrange, sizeof(int2) * h->cap);
-    int n_e = 0, n_r = 0, e_pairs = 0;
+    int n_e = 0, n_r = 0;
     size_t max_hist = 0;
     int n_most = 0;
-    for (const Chain& c : h->chains) {
-        e_pairs += energy_pairs(c.nb);
-        n_most = std::max(n_most, c.n);
-    }
+    for (const Chain& c : h->chains) n_most = std::max(n_most, c.n);
     for (Chain& c : h->chains) {
-        c.e_split = energy_split(c.nb, e_pairs);
+        c.e_split = energy_split(c.nb);
         n_e += energy_pairs(c.nb) * c.e_split;
         n_r += c.nb;
         const size_t nt = c.species.size();
