@@ -8,12 +8,10 @@ pytestmark = pytest.mark.gpu
 
 
 def test_refused_surrogate_changes_nothing():
-    import torch
     from paper_1602_05716_amd import inputs, mc, surrogate
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
     sy = inputs.electrolyte(160, 160, 1.0, -1.0, 1.0, 1.0, 0.02, 0.7)
     sy.xyz = inputs.random_start(sy, 5)
-    many = [sy] * (cus + 20)
+    many = [sy] * 276  # 256 compute units
     opts = dict(precision="fp32", waves=4, resum_every=0, da_window=3)
     got = []
     for refuse in (False, True):
