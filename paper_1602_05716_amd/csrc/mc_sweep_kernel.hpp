@@ -858,6 +858,7 @@ __device__ __forceinline__ void da_hist_add(SH& sh, const ChainDesc& cd, float i
 typedef short da_bf16x4 __attribute__((ext_vector_type(4)));
 typedef float da_f32x16 __attribute__((ext_vector_type(16)));
 typedef float da_f32x2 __attribute__((ext_vector_type(2)));
+typedef float da_f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 da_pair __attribute__((ext_vector_type(2)));
 
 // two floats rounded to bfloat16 (to nearest even), in one word
@@ -902,13 +903,17 @@ __device__ __forceinline__ void da_network(SweepShared<T, M, true>& sh, const Ch
     static_assert(M == 4, "the network phase assumes 4 waves");
     const int half = lane >> 5, row = wave * 32 + (lane & 31), mover = row & 63, pos = row >> 6;
     const __amdgpu_buffer_rsrc_t wbr = make_rsrc((void*)cd.da_w1b, (uint32_t)(4u * kDaIn * kDaHid));
-    // 4 consecutive inputs k of hidden unit `unit` of layer `layer`
-    auto weights = [&](int layer, int unit, int k) -> da_bf16x4 {
+    // inputs 8 j + 4 half .. + 3 of hidden unit 32 t + lane % 32 of layer
+    // `layer` (the part common to all in one register, worked out here: kept
+    // from target to target, an offset each would not fit the registers)
+    int w_lane = (lane & 31) * kDaIn + 4 * half;
+    if constexpr (!SweepShared<T, M, true>::kWtsLds) asm volatile("" : "+v"(w_lane));
+    auto weights = [&](int layer, int t, int j) __attribute__((always_inline)) -> da_bf16x4 {
         if constexpr (SweepShared<T, M, true>::kWtsLds)
-            return *reinterpret_cast<const da_bf16x4*>(&sh.wts[layer * kDaHid + unit][k]);
+            return *reinterpret_cast<const da_bf16x4*>(&sh.wts[layer * kDaHid + 32 * t + (lane & 31)][8 * j + 4 * half]);
         else
             return __builtin_bit_cast(da_bf16x4, __builtin_amdgcn_raw_buffer_load_b64(
-                                                     wbr, (uint32_t)(2 * ((layer * kDaHid + unit) * kDaIn + k)), 0, 0));
+                                                     wbr, 2 * w_lane, 2 * ((layer * kDaHid + 32 * t) * kDaIn + 8 * j), 0));
     };
     __syncthreads();  // every histogram add of this target is done
 #ifdef MC_TIMELINE
@@ -939,8 +944,13 @@ __device__ __forceinline__ void da_network(SweepShared<T, M, true>& sh, const Ch
             constexpr DaPair d = da_pair_at(p);
 #pragma unroll
             for (int u = 0; u < 2; ++u)
-                wt[p % kAhead][u] = weights(d.layer, 32 * (d.t + u) + (lane & 31), 8 * d.j + 4 * half);
+                wt[p % kAhead][u] = weights(d.layer, d.t + u, d.j);
         };
+        // (one address for every bias read, worked out here: an address each
+        // would be kept from target to target, a register each)
+        typedef __attribute__((address_space(3))) const da_f32x4 lds_f32x4;
+        lds_f32x4* bias = (lds_f32x4*)&sh.bias[0][4 * half];
+        asm volatile("" : "+v"(bias));
         uint2 x[kDaIn / 8], h[kDaHid / 8];
         auto convert = [&](int j) {
             // counts up to 255 are bfloat16 values: the upper halves of the floats
@@ -953,7 +963,7 @@ __device__ __forceinline__ void da_network(SweepShared<T, M, true>& sh, const Ch
         da_f32x16 acc1[4], acc2[4];
         // bf16(relu(acc + bias)) of units 8 j + 4 half .. + 3
         auto activation = [&](const da_f32x16 (&acc)[4], int which, int j) {
-            const float4 b = *reinterpret_cast<const float4*>(&sh.bias[which][8 * j + 4 * half]);
+            const da_f32x4 b = bias[which * (kDaHid / 4) + 2 * j];
             const float bv[4] = {b.x, b.y, b.z, b.w};
             float r[4];
 #pragma unroll
@@ -969,7 +979,7 @@ __device__ __forceinline__ void da_network(SweepShared<T, M, true>& sh, const Ch
         float part[4][4];
         auto last_layer = [&](int j) {
             const uint2 a = activation(acc2, 1, j);
-            const float4 w = *reinterpret_cast<const float4*>(&sh.bias[2][8 * j + 4 * half]);
+            const da_f32x4 w = bias[2 * (kDaHid / 4) + 2 * j];
             const float wv[4] = {w.x, w.y, w.z, w.w};
             const uint32_t hb[4] = {a.x << 16, a.x & 0xFFFF0000u, a.y << 16, a.y & 0xFFFF0000u};
 #pragma unroll
@@ -1029,7 +1039,8 @@ __device__ __forceinline__ void da_network(SweepShared<T, M, true>& sh, const Ch
 // the targets g = k_wg (mod the chain's workgroup count).
 template <typename T, int M, bool UNIFORM_SIGMA, bool DA>
 __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const ChainDesc& cd, const int k_wg,
-                                            uint32_t s0, int32_t n_sweeps, const Ctl& ctl)
+                                            uint32_t s0, int32_t n_sweeps, const Ctl& ctl, const int wave,
+                                            const int lane)
 {
     using T4 = typename Prec<T>::T4;
     using IO = PosIO<T>;
@@ -1039,9 +1050,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
     static_assert(KB >= LC, "the chain step's band slots are band groups");
     using SB = typename SliceBits<P>::type;
 
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-
+    const int tid = 64 * wave + lane;  // (threadIdx.x itself would hold a register throughout)
     const int nb = cd.nb, band = cd.band;
     const int npad = nb * kGroup;
     const __amdgpu_buffer_rsrc_t pos_r = make_rsrc(cd.pos, (uint32_t)(2u * npad * IO::kBytes));
@@ -1053,7 +1062,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
     const int64_t g_begin = (int64_t)s0 * nb;
     const int64_t g_end = g_begin + (int64_t)n_sweeps * nb;
 
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         // one store each (a merged 64-bit store of zeros has kept a register
         // pair live through the whole kernel)
         __hip_atomic_store(&sh.ready, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1063,7 +1072,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
     }
     if constexpr (DA) {
         static_assert(sizeof(sh.hist) == sizeof(uint32_t) * kGroup * 65, "histogram rows");
-        for (int k = threadIdx.x; k < kGroup * 65; k += 64 * M) (&sh.hist[0][0])[k] = 0u;
+        for (int k = tid; k < kGroup * 65; k += 64 * M) (&sh.hist[0][0])[k] = 0u;
     }
     // the delayed-acceptance switch is constant during a launch (the drift
     // monitor changes it between launches)
@@ -1071,8 +1080,8 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
     const float inv_dr = DA ? (float)(1.0 / cd.da_dr) : 0.f;
     if constexpr (DA) {
         if (da_on) {
-            if (threadIdx.x == 0) sh.bias3 = cd.da_w[kDaParams - 1];
-            for (int k = threadIdx.x; k < 3 * kDaHid; k += 64 * M) {
+            if (tid == 0) sh.bias3 = cd.da_w[kDaParams - 1];
+            for (int k = tid; k < 3 * kDaHid; k += 64 * M) {
                 const int u = k % kDaHid, o_b2 = kDaIn * kDaHid + kDaHid + kDaHid * kDaHid;
                 sh.bias[k / kDaHid][u] = cd.da_w[(k < kDaHid ? kDaIn * kDaHid : k < 2 * kDaHid ? o_b2 : o_b2 + kDaHid) + u];
             }
@@ -1081,7 +1090,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
     if constexpr (SweepShared<T, M, DA>::kWtsLds) {
         if (da_on) {
             static_assert(kDaIn == kDaHid, "both matrices are 128 x 128");
-            for (int k = threadIdx.x; k < 2 * kDaHid * kDaIn / 4; k += 64 * M) {
+            for (int k = tid; k < 2 * kDaHid * kDaIn / 4; k += 64 * M) {
                 const int row = k / (kDaIn / 4), c4 = k % (kDaIn / 4);  // row of the two stacked matrices
                 const uint16_t* src = row < kDaHid ? cd.da_w1b + row * kDaIn : cd.da_w2b + (row - kDaHid) * kDaIn;
                 *reinterpret_cast<uint2*>(&sh.wts[row][4 * c4]) = *reinterpret_cast<const uint2*>(src + 4 * c4);
@@ -1657,10 +1666,11 @@ sweep_kernel(const ChainDesc* __restrict__ chains, const int2* __restrict__ wg_r
              const int2* __restrict__ items, uint32_t s0, int32_t n_sweeps, Ctl ctl)
 {
     __shared__ SweepShared<T, M, DA> sh;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int2 r = wg_range[blockIdx.x];
     for (int q = r.x; q < r.y; ++q) {
         const int2 it = items[q];
-        sweep_chain<T, M, UNIFORM_SIGMA, DA>(sh, chains[it.x], it.y, s0, n_sweeps, ctl);
+        sweep_chain<T, M, UNIFORM_SIGMA, DA>(sh, chains[it.x], it.y, s0, n_sweeps, ctl, wave, lane);
     }
 }
 
