@@ -369,6 +369,7 @@ rdf_scan_kernel(const ChainDesc* __restrict__ chains)
     __shared__ int wsum[16];
     const ChainDesc& cd = chains[blockIdx.x];
     const int cells = cd.rdf_side * cd.rdf_side * cd.rdf_side;
+    if (cells == 0) return;  // a chain without a grid
     int* __restrict__ count = cd.rdf_cells;
     int* __restrict__ start = cd.rdf_start;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;

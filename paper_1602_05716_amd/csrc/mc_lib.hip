@@ -129,7 +129,8 @@ struct Chain {
     double* sweep_tot = nullptr;  // [kMaxLaunchSweeps]
     unsigned long long* rdf_counts = nullptr;
     unsigned long long* rdf_centres = nullptr;
-    int rdf_side = 0;             // cell grid of the pair counts (see rdf_grid)
+    bool on_grid = false;         // pair counts on a cell grid, not over all pairs
+    int rdf_side = 0;             // the grid (see rdf_grid), 0 without
     double rdf_h = 1.0;
     int32_t* rdf_cells = nullptr; // [rdf_side^3]
     int32_t* rdf_start = nullptr; // [rdf_side^3 + 1]
@@ -185,10 +186,9 @@ struct mc_handle {
     int2* d_wgrange = nullptr;    // [cap] per workgroup: its items [begin, end)
     BlockItem* d_eitems = nullptr;   // energy re-sum blocks
     int n_eitems = 0;
-    BlockItem* d_ritems = nullptr;   // g(r) blocks
-    int n_ritems = 0;
+    BlockItem* d_ritems = nullptr;   // g(r) blocks: of the chains over all pairs, then of those on a grid
+    int n_rpairs = 0, n_rgrid = 0;
     size_t rdf_lds = 0;
-    bool rdf_cells = false;       // pair counts on the cell grid, not over all pairs
     // sweep-kernel timing (record_timing)
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_pending;
     std::vector<int64_t> ev_sweeps;
@@ -662,18 +662,17 @@ int launch_rdf(mc_handle* h) {
     const int parity = (int)((h->sweeps - 1) & 1);
     auto launch = [&](auto zero) {
         using T = decltype(zero);
-        if (!h->rdf_cells) {
-            hipLaunchKernelGGL(rdf_kernel<T>, dim3(h->n_ritems), dim3(256), h->rdf_lds, h->stream, h->d_desc,
+        if (h->n_rpairs)
+            hipLaunchKernelGGL(rdf_kernel<T>, dim3(h->n_rpairs), dim3(256), h->rdf_lds, h->stream, h->d_desc,
                                h->d_ritems, parity, rmax, dr, bins);
-            return;
-        }
-        hipLaunchKernelGGL(rdf_bin_kernel<T>, dim3(h->n_ritems), dim3(64), 0, h->stream, h->d_desc, h->d_ritems,
-                           parity);
+        if (!h->n_rgrid) return;
+        const BlockItem* on_grid = h->d_ritems + h->n_rpairs;
+        hipLaunchKernelGGL(rdf_bin_kernel<T>, dim3(h->n_rgrid), dim3(64), 0, h->stream, h->d_desc, on_grid, parity);
         hipLaunchKernelGGL(rdf_scan_kernel, dim3((unsigned)h->chains.size()), dim3(1024), 0, h->stream, h->d_desc);
-        hipLaunchKernelGGL(rdf_scatter_kernel<T>, dim3(h->n_ritems), dim3(64), 0, h->stream, h->d_desc, h->d_ritems,
+        hipLaunchKernelGGL(rdf_scatter_kernel<T>, dim3(h->n_rgrid), dim3(64), 0, h->stream, h->d_desc, on_grid,
                            parity);
-        hipLaunchKernelGGL(rdf_count_kernel<T>, dim3(std::min(h->n_ritems, 2 * h->dev.cus)), dim3(64 * kRdfWaves),
-                           h->rdf_lds, h->stream, h->d_desc, h->d_ritems, h->n_ritems, rmax, dr, bins);
+        hipLaunchKernelGGL(rdf_count_kernel<T>, dim3(std::min(h->n_rgrid, 2 * h->dev.cus)), dim3(64 * kRdfWaves),
+                           h->rdf_lds, h->stream, h->d_desc, on_grid, h->n_rgrid, rmax, dr, bins);
     };
     if (h->fp64)
         launch(0.0);
@@ -985,26 +984,42 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
     plan.add(&h->d_desc, sizeof(ChainDesc) * n_chains);
     plan.add(&h->d_wgmap, sizeof(int2) * (h->cap + n_chains));
     plan.add(&h->d_wgrange, sizeof(int2) * h->cap);
-    int n_e = 0, n_r = 0;
+    int n_e = 0;
     size_t max_hist = 0;
     int n_most = 0;
     for (const Chain& c : h->chains) n_most = std::max(n_most, c.n);
+    // Chains whose pair counts go over a cell grid: by the work that testing
+    // all pairs makes of them, N a share of N that grows with the range rmax = f R
+    // (more pairs to bin).  While the handle's groups do not fill the device,
+    // the grid's four launches cost 80-90 us whatever the size, testing all
+    // pairs at f = 0.03 / 0.1 / 0.25 / 0.5 78 / 80 / 115 / 191 us at N = 2000 (37
+    // to 94 at 1000) and 139 / 150 / 209 / 328 for two chains of 4000.  In a full
+    // device the grid takes 2 to 2.8 ns an ion and testing all pairs 0.47 / 0.50
+    // / 0.85 / 1.0 ns times N / 1000: 250 chains of 2000 1.40 / 1.27 / 1.37 / 1.21
+    // ms on grids, 0.47 / 0.51 / 1.01 / 1.21 over all pairs; 128 of 4000 1.03 /
+    // 1.00 / 0.89 / 0.66 and 0.88 / 0.98 / 1.71 / 2.08; 64 of 8000 0.98-1.05 and
+    // 1.6-4.1.  Where the device is not full, small chains go along with a
+    // larger one's launches (20 of 500 to 900 beside one of 7966: 102-110 us, and
+    // 130-148 with their own launch over all pairs).
+    const bool few = groups < 2 * h->dev.cus;
+    bool any_on_grid = false;
+    for (Chain& c : h->chains) {
+        const double work = c.n * std::min(1.0, 0.35 + 2.0 * opt.rdf_rmax / c.R);
+        c.on_grid = few ? c.n >= 2000 && work >= 1100.0 : work >= 2200.0;
+        any_on_grid |= c.on_grid;
+    }
     for (Chain& c : h->chains) {
         c.e_split = energy_split(c.nb);
         n_e += energy_pairs(c.nb) * c.e_split;
-        n_r += c.nb;
+        c.on_grid |= few && any_on_grid;
+        (c.on_grid ? h->n_rgrid : h->n_rpairs) += c.nb;
         const size_t nt = c.species.size();
         max_hist = std::max(max_hist, nt * nt * (size_t)opt.rdf_bins);
     }
     h->n_eitems = n_e;
-    h->n_ritems = n_r;
     h->rdf_lds = sizeof(unsigned int) * max_hist;
-    // The cell grid's four launches cost 70-80 us whatever the size; testing
-    // all pairs takes 75-180 us at N = 2001 (range 0.1 to 0.5 R), 37-94 at
-    // 1000, 140-330 at 4001.
-    h->rdf_cells = n_most >= 2000;
     plan.add(&h->d_eitems, sizeof(BlockItem) * n_e);
-    plan.add(&h->d_ritems, sizeof(BlockItem) * n_r);
+    plan.add(&h->d_ritems, sizeof(BlockItem) * (h->n_rpairs + h->n_rgrid));
     for (Chain& c : h->chains) {
         const size_t nt = c.species.size();
         plan.add(&c.pos, 2 * t4 * c.npad);
@@ -1022,7 +1037,7 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
         plan.add(&c.sweep_tot, sizeof(double) * kMaxLaunchSweeps);
         plan.add(&c.rdf_counts, sizeof(unsigned long long) * nt * nt * opt.rdf_bins);
         plan.add(&c.rdf_centres, sizeof(unsigned long long) * nt);
-        if (h->rdf_cells) {
+        if (c.on_grid) {
             rdf_grid(c.n, c.R, opt.rdf_rmax, &c.rdf_side, &c.rdf_h);
             const size_t cells = (size_t)c.rdf_side * c.rdf_side * c.rdf_side;
             plan.add(&c.rdf_cells, sizeof(int32_t) * cells);
@@ -1058,11 +1073,14 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
 
     // host images and uploads, chain by chain
     std::vector<BlockItem> eitems, ritems;
+    for (const bool grid : {false, true})
+        for (int k = 0; k < n_chains; ++k)
+            for (int r = 0; r < h->chains[k].nb && h->chains[k].on_grid == grid; ++r)
+                ritems.push_back(BlockItem{k, r});
     for (int k = 0; k < n_chains; ++k) {
         Chain& c = h->chains[k];
         const mc_chain_spec& sp = specs[k];
         for (int p = 0; p < energy_pairs(c.nb) * c.e_split; ++p) eitems.push_back(BlockItem{k, p});
-        for (int r = 0; r < c.nb; ++r) ritems.push_back(BlockItem{k, r});
         // positions carry the version tag of the sweep that produced them;
         // the initial state is the result of virtual sweeps -2 (parity 0)
         // and -1 (parity 1)
