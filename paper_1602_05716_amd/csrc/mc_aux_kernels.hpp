@@ -42,8 +42,8 @@ struct ReportSource {
 
 // The report to r and count values of the packed positions to xyz, both
 // pinned host memory, four values a thread (xyz has room for whole fours).
-// Bound: one launch and one wait, 9 us in all; a copy per item into pageable
-// memory took 10 us each.
+// Bound: one launch and one wait, 12 us a read in all (2.8 of them the kernel);
+// a copy per item into pageable memory took 10 us each.
 template <typename T, typename T4>
 __global__ void __launch_bounds__(256)
 report_kernel(ReportSource s, ChainReport* __restrict__ r, const T4* __restrict__ pos, int count, T* __restrict__ xyz)
@@ -312,6 +312,9 @@ rdf_kernel(const ChainDesc* __restrict__ chains, const BlockItem* __restrict__ i
 // then costs more than they save).  The side is a hair above rmax / 2, so
 // that rounding in the cell index never puts a pair in range more than two
 // cells apart.
+// The most cells across, 24 / 32 / 40 / 48 / 64, in one sample: 437 / 348 / 334 /
+// 345 / 348 us at N = 131072 (range 0.02 R), 1162 / 743 / 617 / 617 / 617 at 262144
+// (0.02 R), 1246 / 826 / 758 / 809 / 805 (0.1 R).
 constexpr int kRdfReach = 2;
 constexpr int kRdfMaxSide = 40;
 inline void rdf_grid(int n, double R, double rmax, int* side, double* h) {

@@ -900,7 +900,9 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
     // evaluate both outcomes of every partner, which in a short chain is more
     // work than the wait it hides.  Ten sweeps with bands 1 / 2 / 4: 251 / 268
     // / 310 us at N = 512, 408 / 403 / 444 at 1000, 725 / 689 / 723 at 2000;
-    // 1.34 / 1.26 / 1.28 ms at 4000.  (A float chain's band also fixes which
+    // 1.34 / 1.26 / 1.28 ms at 4000; with per-ion diameters 608 / 505 / 544 us at
+    // 1002, 1.15 / 0.85 / 0.88 ms at 2001, 2.15 / 1.60 / 1.52 at 3999.  Four sweeps
+    // of 256 chains of 2000: 7.5 / 7.7 / 8.2 ms.  (A float chain's band also fixes which
     // float sums its terms are grouped in, so it is left as it is.)
     if (opt.band < 0 && h->fp64 && opt.log_moves == 0)
         for (Chain& c : h->chains)
@@ -965,7 +967,10 @@ int create_handle(int32_t n_chains, const mc_chain_spec* specs, const mc_options
         // double kernels wait for the pair terms of the newest decided groups
         // at every size, and twice the waves halve that wait: ten sweeps in
         // 113 us instead of 136 at N = 64, 0.50 ms instead of 0.59 at 1000,
-        // 1.38 instead of 1.69 at 4000, 18.6 instead of 22.9 at 32768.
+        // 1.38 instead of 1.69 at 4000, 18.6 instead of 22.9 at 32768; with
+        // per-ion diameters 0.51 instead of 0.59 at 1002, 1.52 instead of 1.83 at
+        // 3999, 2.84 instead of 3.45 at 8001.  Four sweeps of the 256-chain
+        // ensemble: 114 instead of 141 ms.
         if (h->fp64 && opt.waves == 0 && opt.log_moves == 0 && residents(pick_sweep(true, 8, h->uniform_sigma), 8) >= h->cap)
             h->waves = 8;
     }

@@ -267,8 +267,12 @@ constexpr int kDecidedSlice = (sizeof(T) == 4 && M == 8 && !DA) ? 64 : kGroup / 
 constexpr int kPatientDistance = 6;
 
 // Decided groups this close before the last one the target waits for are taken
-// one at a time.
+// one at a time (at least one group, which empties the ring below).  Nearer, a
+// round of four waits for its newest group: ten sweeps with 4 / 8 / 12 / 20 / 32
+// of them 1.31 / 1.21 / 1.20 / 1.21 / 1.23 ms at N = 2048, 2.21 / 2.01 / 1.92 /
+// 1.89 / 1.90 at 4096, 12.85 / 12.63 / 12.62 / 12.64 / 12.66 at 32768.
 constexpr int kQuadMargin = 12;
+static_assert(kQuadMargin >= 1, "the ring is emptied in the rounds of one group");
 // Entries of a wave's ring of near partners: one partner adds up to 64, and
 // the ring is emptied by 64 as soon as it holds that many.
 constexpr int kNearRing = 128;
@@ -1395,7 +1399,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                 // which the chain is still deciding.  Bound: the pair terms;
                 // one slice at a time, with one workgroup a CU, every slice
                 // waited for its records (ten sweeps of N = 32768 14.6 ms,
-                // 13.0 so).  The plain kernels have a second workgroup to fill
+                // 13.0 so, 12.7 with the weights' rows aligned).  The plain kernels have a second workgroup to fill
                 // that wait: no gain at N = 32768, 3 % lost at 4001.
                 if constexpr (DA && UNIFORM_SIGMA && SweepShared<T, M, DA>::SW == kGroup) {
                     const int64_t q_last = g_last - kQuadMargin;
@@ -1463,8 +1467,9 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                         slice_uniform = __ballot(lane < PD && hjl != hj0) == 0ull;
                     }
                     wave_lds_sync();
-                    // (KD steps of one, compared one by one, were 1.2 % of a sweep
-                    // of N = 131072: 7.95 ms, 7.86 so)
+                    // (KD steps of one, compared one by one, were about 1 % of a
+                    // sweep of N = 131072: 7.95 ms, 7.86 so, of runs that differ by
+                    // 0.3 %)
                     int bn = bp + KD;
                     int64_t sn = sp;
                     while (bn >= nb) {
