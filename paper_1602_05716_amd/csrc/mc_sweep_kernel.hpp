@@ -269,8 +269,8 @@ constexpr int kPatientDistance = 6;
 // Decided groups this close before the last one the target waits for are taken
 // one at a time (at least one group, which empties the ring below).  Nearer, a
 // round of four waits for its newest group: ten sweeps with 4 / 8 / 12 / 20 / 32
-// of them 1.31 / 1.21 / 1.20 / 1.21 / 1.23 ms at N = 2048, 2.21 / 2.01 / 1.92 /
-// 1.89 / 1.90 at 4096, 12.85 / 12.63 / 12.62 / 12.64 / 12.66 at 32768.
+// of them 0.934 / 0.890 / 0.893 / 0.893 / 0.901 ms at N = 2048, 1.70 / 1.67 / 1.67 /
+// 1.67 / 1.67 at 4096, 12.28 / 12.25 / 12.24 / 12.21 / 12.22 at 32768.
 constexpr int kQuadMargin = 12;
 static_assert(kQuadMargin >= 1, "the ring is emptied in the rounds of one group");
 // Entries of a wave's ring of near partners: one partner adds up to 64, and
@@ -1324,7 +1324,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                 // smallest trial distance is below the contact distance
                 T d2t_min = (T)3.0e38;
                 // Delayed acceptance: the partners within range of a mover are
-                // few (one in a thousand pairs at the usual range), so they
+                // few (one in a thousand pairs in a large system), so they
                 // are only noted in the pair loop, as a ballot per partner,
                 // and go to the wave's ring; the exact distances and bins (a
                 // double sqrt and division each) are worked out for 64 of
@@ -1348,26 +1348,40 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                     q_out += count;
                     wave_lds_sync();
                 };
-                // to the ring: the movers near_of[m] near partner st[m]
+                // to the ring: the movers near_of[m] near partner st[m], every
+                // lane one of its own partners a turn.  Partner by partner, a tile
+                // with several near pairs, as in small systems, took up to 16
+                // turns of a few lanes: ten sweeps of the 2:1 system at N = 8001
+                // with a move log 3.58 ms, 2.7 so.  A turn of 40 lanes and more is
+                // binned at once: of the same system with every partner in range
+                // four sweeps take 4.85 ms instead of 6.0 (8001, log), at the
+                // cost of 1 % where near pairs are few (ten of N = 32768 12.2 ms,
+                // 12.1 without; lines at 32 to 48 within 1 %, 56 up to 2.5 % slower).
                 auto note_near = [&](const T4* st, const uint64_t (&near_of)[DA ? P : 1], uint64_t near_any) {
-                    if (near_any != 0ull) {
+                    if (near_any == 0ull) return;
+                    uint32_t mine = 0;
 #pragma unroll
-                        for (int m = 0; m < P; ++m) {
-                            if (near_of[m] != 0ull) {
-                                const T4 p = st[m];
-                                const double qq = (double)p.w * (double)qi;
-                                const bool put = ((near_of[m] >> lane) & 1ull) != 0 && qq != 0.0;
-                                const uint64_t who = __ballot(put);
-                                if (put)
-                                    sh.near[wave][(q_in + __builtin_amdgcn_mbcnt_hi(
-                                                              (uint32_t)(who >> 32),
-                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u))) &
-                                                  (kNearRing - 1)] =
-                                        mk4<T>(p.x, p.y, p.z, (T)(lane + (qq < 0.0 ? 64 : 0)));
-                                q_in += (uint32_t)__popcll(who);
-                                if (q_in - q_out >= 64u) bin_near(64u);
+                    for (int m = 0; m < (DA ? P : 1); ++m)
+                        mine |= __builtin_amdgcn_inverse_ballot_w64(near_of[m]) ? 1u << m : 0u;
+                    while (__ballot(mine != 0u) != 0ull) {
+                        const T4 p = st[mine ? __builtin_ctz(mine) : 0];
+                        const double qq = (double)p.w * (double)qi;
+                        const bool put = mine != 0u && qq != 0.0;
+                        mine &= mine - 1u;
+                        const uint64_t who = __ballot(put);
+                        if (__popcll(who) >= 40) {
+                            if (put) {
+                                da_hist_add(sh, cd, inv_dr, lane, 0, qq < 0.0, d2_exact(xi, yi, zi, p.x, p.y, p.z));
+                                da_hist_add(sh, cd, inv_dr, lane, 1, qq < 0.0, d2_exact(txi, tyi, tzi, p.x, p.y, p.z));
                             }
+                            continue;
                         }
+                        if (put)
+                            sh.near[wave][(q_in + __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
+                                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u))) &
+                                          (kNearRing - 1)] = mk4<T>(p.x, p.y, p.z, (T)(lane + (qq < 0.0 ? 64 : 0)));
+                        q_in += (uint32_t)__popcll(who);
+                        if (q_in - q_out >= 64u) bin_near(64u);
                     }
                 };
                 // a working-precision squared distance below this bound may be
@@ -1399,7 +1413,7 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                 // which the chain is still deciding.  Bound: the pair terms;
                 // one slice at a time, with one workgroup a CU, every slice
                 // waited for its records (ten sweeps of N = 32768 14.6 ms,
-                // 13.0 so, 12.7 with the weights' rows aligned).  The plain kernels have a second workgroup to fill
+                // 13.0 so).  The plain kernels have a second workgroup to fill
                 // that wait: no gain at N = 32768, 3 % lost at 4001.
                 if constexpr (DA && UNIFORM_SIGMA && SweepShared<T, M, DA>::SW == kGroup) {
                     const int64_t q_last = g_last - kQuadMargin;
