@@ -1413,8 +1413,9 @@ __device__ __forceinline__ void sweep_chain(SweepShared<T, M, DA>& sh, const Cha
                 // which the chain is still deciding.  Bound: the pair terms;
                 // one slice at a time, with one workgroup a CU, every slice
                 // waited for its records (ten sweeps of N = 32768 14.6 ms,
-                // 13.0 so, with near partners still taken one by one).  The plain kernels have a second workgroup to fill
-                // that wait: no gain at N = 32768, 3 % lost at 4001.
+                // 13.0 so, with near partners still taken one by one).  The
+                // plain kernels have a second workgroup to fill that wait: no
+                // gain at N = 32768, 3 % lost at 4001.
                 if constexpr (DA && UNIFORM_SIGMA && SweepShared<T, M, DA>::SW == kGroup) {
                     const int64_t q_last = g_last - kQuadMargin;
                     const int sub = lane / P, jq = wave * P + lane % P;
